@@ -541,7 +541,8 @@ uc_status uc_calibrate_policy(const float* frac, int rows, int n_types, double t
 /* Kernel path selection for uc_attend_mixed (process-wide; for cross-checks):
  * UC_PATH_AUTO (default) uses the matrix-core kernels where the inputs allow
  * (bf16 rows and queries, D = 128, at most 16 query rows per KV head for
- * decode), UC_PATH_VALU forces the vector-ALU kernels for every input.
+ * decode; binary32 matrix products for every other input), UC_PATH_VALU
+ * forces the vector-ALU kernels for every input.
  * Returns the previous setting, or -1 for an unknown value. */
 #define UC_PATH_AUTO 0
 #define UC_PATH_VALU 1
@@ -676,7 +677,9 @@ const char* uc_last_error(void);
 /* Name of the main kernel the calling thread's last successful launch of
  * uc_attend_mixed, uc_attend_append, uc_attend_batch or uc_score_importance
  * ran ("decode_mfma", "decode_mfma_append", "prefill_mfma", "attend_valu",
- * "decode_batch", "score_mfma", "score_valu"; "" before any).  Lets tests
+ * "decode_batch", "score_mfma", "score_valu"; "" before any).  The two
+ * "_valu" names stand for the binary32 path: its matrix-core kernels under
+ * UC_PATH_AUTO, the vector-ALU ones under UC_PATH_VALU.  Lets tests
  * assert the path a case reaches; static storage, never freed. */
 const char* uc_last_kernel(void);
 

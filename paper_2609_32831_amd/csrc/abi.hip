@@ -222,6 +222,9 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // segments with fewer rows (min(max_chunks, ceil(n / rows_min)) per segment),
 // so a workspace sized at the largest row counts serves smaller ones.
 constexpr int kAttRows = 256, kAttMaxChunks = 64, kLseRows = 512, kLseMaxChunks = 32;
+// records of a finely cut call may take this much (well inside the static
+// array of uc_attend_mixed_noalloc, so no call outgrows it)
+constexpr size_t kFineBytes = 8u << 20;
 
 size_t generic_ws(const uc_shape& sh, const KSegs& ks, int rows_min, int max_chunks, int M,
                   bool want_o) {
@@ -232,9 +235,51 @@ size_t generic_ws(const uc_shape& sh, const KSegs& ks, int rows_min, int max_chu
   return align256((size_t)sh.B * sh.Hq * M * chunks * stride * sizeof(float));
 }
 
-ChunkPlan attend_plan(const KSegs& ks) { return make_plan(ks, kAttRows, kAttMaxChunks); }
-ChunkPlan score_lse_plan(const KSegs& ks) { return make_plan(ks, kLseRows, kLseMaxChunks); }
-ChunkPlan score_col_plan(const KSegs& ks) { return make_plan(ks, 256, 1 << 20); }
+// The binary32 matrix-core kernel takes 16 query rows of a KV head per
+// workgroup and at least 64 rows (a tile per wave).  Chunks are cut so that
+// about three workgroups per CU exist: fewer left the short calls waiting on
+// one memory latency per tile, more only adds records to merge.  The chunk
+// bound (at most wgs + n_segs, at most one per 64 rows) never shrinks as
+// rows are added.
+int wide_wgs(const uc_shape& sh, int M) {
+  const int64_t blocks = ((int64_t)(sh.Hq / sh.Hkv) * M + 15) / 16 * sh.B * sh.Hkv;
+  return (int)std::max<int64_t>(1, 3 * device_cus() / blocks);
+}
+bool wide_ok(const uc_shape& sh, int M) {  // the launch's grid limits
+  return ((int64_t)(sh.Hq / sh.Hkv) * M + 15) / 16 <= 65535 && (int64_t)sh.B * sh.Hkv <= 65535;
+}
+size_t wide_bytes(const uc_shape& sh, const KSegs& ks, int M, bool want_o) {
+  size_t fine = 0;
+  for (int i = 0; i < ks.n; ++i) fine += (ks.s[i].n_rows + 63) / 64;
+  const size_t chunks = std::min<size_t>(fine, (size_t)wide_wgs(sh, M) + ks.n);
+  return align256((size_t)sh.B * sh.Hq * M * chunks * (want_o ? sh.D + 2 : 2) * sizeof(float));
+}
+ChunkPlan wide_plan(const uc_shape& sh, const KSegs& ks, int M) {
+  int64_t total = 0;
+  for (int i = 0; i < ks.n; ++i) total += ks.s[i].n_rows;
+  const int64_t per = (total + wide_wgs(sh, M) - 1) / wide_wgs(sh, M);
+  return make_plan(ks, (int)std::min<int64_t>((std::max<int64_t>(per, 1) + 63) / 64 * 64, 1 << 30),
+                   1 << 30);
+}
+bool wide_path(const uc_shape& sh, int M) { return g_path.load() == UC_PATH_AUTO && wide_ok(sh, M); }
+
+// Attention outside the bf16 kernels: the fine cut when its records are few
+// (one query block against a long cache), else the coarse one, which many
+// query blocks fill the chip with.
+ChunkPlan attend_plan(const uc_shape& sh, const KSegs& ks, int M) {
+  if (wide_path(sh, M) && wide_bytes(sh, ks, M, true) <= kFineBytes) return wide_plan(sh, ks, M);
+  return make_plan(ks, kAttRows, kAttMaxChunks);
+}
+size_t attend_ws(const uc_shape& sh, const KSegs& ks, int M) {
+  return std::max(generic_ws(sh, ks, kAttRows, kAttMaxChunks, M, true),
+                  std::min(wide_bytes(sh, ks, M, true), kFineBytes));
+}
+ChunkPlan score_lse_plan(const uc_shape& sh, const KSegs& ks, int W) {
+  return wide_path(sh, W) ? wide_plan(sh, ks, W) : make_plan(ks, kLseRows, kLseMaxChunks);
+}
+ChunkPlan score_col_plan(const uc_shape& sh, const KSegs& ks, int W) {
+  return make_plan(ks, wide_path(sh, W) ? score_wide_chunk_rows() : 256, 1 << 30);
+}
 
 uc_status launched(hipError_t e) {
   if (e != hipSuccess) return fail(UC_E_DEVICE, "HIP launch error: %s", hipGetErrorString(e));
@@ -289,7 +334,7 @@ size_t uc_attend_workspace_size(const uc_shape* shape, const uc_segment* segs, i
     return decode_mfma_workspace(*shape, ks, M);
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M))
     return prefill_mfma_workspace(*shape, ks);
-  return generic_ws(*shape, ks, kAttRows, kAttMaxChunks, M, true);
+  return attend_ws(*shape, ks, M);
 }
 
 uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
@@ -319,15 +364,20 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_s
     g_last_kernel = "prefill_mfma";
     return launched(launch_prefill_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, s));
   }
-  const ChunkPlan p = attend_plan(ks);
-  const size_t need = generic_ws(*shape, ks, kAttRows, kAttMaxChunks, M, true);
+  const ChunkPlan p = attend_plan(*shape, ks, M);
+  const size_t need = attend_ws(*shape, ks, M);
   if (ws_bytes < need || !ws) return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   float* partial = (float*)ws;
   g_last_kernel = "attend_valu";
   hipError_t e = kernel_timer_begin(s);
-  if (e == hipSuccess) e = launch_attend_generic(*shape, ks, p, q, q_dt, M, sm_scale, partial, true, s);
+  if (e == hipSuccess)
+    e = wide_path(*shape, M)
+            ? launch_attend_wide(*shape, ks, p, q, q_dt, M, sm_scale, partial, true, s)
+            : launch_attend_generic(*shape, ks, p, q, q_dt, M, sm_scale, partial, true, s);
   if (e == hipSuccess) e = kernel_timer_end(s);
-  if (e == hipSuccess) e = launch_attend_combine(*shape, ks, p, M, partial, o, lse, seg_lse, s);
+  if (e == hipSuccess)
+    e = seg_lse ? launch_attend_combine(*shape, ks, p, M, partial, o, lse, seg_lse, s)
+                : launch_record_merge(shape->D, shape->B * shape->Hq * M, p.n_chunks, partial, o, lse, s);
   return launched(e);
 }
 
@@ -509,7 +559,7 @@ uc_status uc_plan_create(const uc_shape* shape, const uc_segment* segs, int n_se
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, kf, q_dt, M)) {
     need = prefill_mfma_workspace(*shape, kf);
   } else {
-    need = generic_ws(*shape, kf, kAttRows, kAttMaxChunks, M, true);
+    need = attend_ws(*shape, kf, M);
     if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(*shape, kf, q_dt, M))
       need = std::max(need, decode_mfma_workspace(*shape, kf, M));
   }
@@ -788,8 +838,11 @@ static void score_ws_parts(const uc_shape& sh, const KSegs& ks, int W, bool fast
       col_b = align256(std::min(qb * base, 512 + base) * score_mfma_chunk_rows() * sizeof(double));
     return;
   }
-  part1 = generic_ws(sh, ks, kLseRows, kLseMaxChunks, W, false);
-  mass_b = align256((size_t)sh.B * sh.Hkv * score_col_plan(ks).n_chunks * sizeof(double));
+  part1 = std::max(generic_ws(sh, ks, kLseRows, kLseMaxChunks, W, false),
+                   wide_bytes(sh, ks, W, false));
+  // chunks of 64 keys, or of 256 on the vector-ALU path
+  mass_b = align256((size_t)sh.B * sh.Hkv * make_plan(ks, score_wide_chunk_rows(), 1 << 30).n_chunks *
+                    sizeof(double));
 }
 
 size_t uc_score_workspace_size(const uc_shape* shape, const uc_segment* segs, int n_segs, int W) {
@@ -818,8 +871,9 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
   const bool fast = score_fast(*shape, ks, q_dt);
   size_t a, b, c, d;
   score_ws_parts(*shape, ks, W, fast, a, b, c, d);
-  if (!ws || ws_bytes < a + b + c + d)
-    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, a + b + c + d);
+  const size_t need = uc_score_workspace_size(shape, segs, n_segs, W);
+  if (!ws || ws_bytes < need)
+    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t s = (hipStream_t)stream;
   float* partial = (float*)ws;
   float* lse = (float*)((char*)ws + a);
@@ -839,12 +893,15 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
       e = launch_score_col_mfma(*shape, ks, p, q_obs, W, W, sm_scale, lse, sp, mpart, colpart, s);
     p2 = p;
   } else {
-    const ChunkPlan p1 = score_lse_plan(ks);
-    p2 = score_col_plan(ks);
-    e = launch_attend_generic(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s);
+    const bool wide = wide_path(*shape, W);
+    const ChunkPlan p1 = score_lse_plan(*shape, ks, W);
+    p2 = score_col_plan(*shape, ks, W);
+    e = wide ? launch_attend_wide(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s)
+             : launch_attend_generic(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s);
     if (e == hipSuccess) e = launch_attend_combine(*shape, ks, p1, W, partial, nullptr, lse, nullptr, s);
     if (e == hipSuccess)
-      e = launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, lse, sp, mpart, s);
+      e = wide ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, lse, sp, mpart, s)
+               : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, lse, sp, mpart, s);
   }
   if (e == hipSuccess && mass_out)
     e = launch_mass_finalize(p2, shape->B * shape->Hkv, n_segs, mpart, mass_out, s);
@@ -869,8 +926,9 @@ uc_status uc_score_columns(const uc_shape* shape, const uc_segment* segs, int n_
   const bool fast = score_fast(*shape, ks, q_dt);
   size_t a, b, c, d;
   score_ws_parts(*shape, ks, W, fast, a, b, c, d);
-  if (!ws || ws_bytes < a + b + c + d)
-    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, a + b + c + d);
+  const size_t need = uc_score_workspace_size(shape, segs, n_segs, W);
+  if (!ws || ws_bytes < need)
+    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   float* sp[kMaxSeg] = {};
   bool any = false;
   if (scores_out)
@@ -890,13 +948,16 @@ uc_status uc_score_columns(const uc_shape* shape, const uc_segment* segs, int n_
   float* lse = (float*)((char*)ws + a);
   double* mpart = mass_out ? (double*)((char*)ws + a + b) : nullptr;
   double* colpart = d ? (double*)((char*)ws + a + b + c) : nullptr;
-  const ChunkPlan p2 = fast ? score_mfma_plan(kp) : score_col_plan(kp);
+  const ChunkPlan p2 = fast ? score_mfma_plan(kp) : score_col_plan(*shape, kp, W);
   hipError_t e = hipSuccess;
   if (p2.n_chunks > 0) {
     e = launch_lse_rows(row_lse, lse_ld, W, shape->B * shape->Hq, lse, s);
     if (e == hipSuccess)
       e = fast ? launch_score_col_mfma(*shape, ks, p2, q_obs, W, (int)q_ld, sm_scale, lse, sp,
                                        mpart, colpart, s)
+          : wide_path(*shape, W)
+               ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, lse, sp,
+                                   mpart, s)
                : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, lse, sp,
                                      mpart, s);
   }

@@ -12,8 +12,8 @@
 // workspace, in base-2 units (logits pre-multiplied by log2(e)); the combine
 // kernel merges them into o, lse and the per-segment lse.
 //
-// This path runs on VALU only.  It serves queries and rows that are not bf16
-// (the bf16 path uses matrix cores) and cross-checks the fast kernels.
+// This path runs on VALU only: it cross-checks the matrix-core kernels
+// (UC_PATH_VALU) and serves calls past their grid limits.
 #include <math.h>
 
 #include "uc_common.h"
@@ -335,13 +335,17 @@ __global__ __launch_bounds__(256) void score_colsum_kernel(KSegs segs, ChunkPlan
     mass_partial[(int64_t)bh * plan.n_chunks + c] = red[0] + red[1] + red[2] + red[3];
 }
 
-__global__ void mass_finalize_kernel(ChunkPlan plan, int nseg, const double* __restrict__ part,
-                                     float* mass) {
-  const int bh = blockIdx.x, a = threadIdx.x;
-  if (a >= nseg) return;
+// grid (b*h_kv, segments), one wave each: the segment's chunk masses, lane
+// sums in chunk order, then the lanes in a fixed order
+__global__ __launch_bounds__(64) void mass_finalize_kernel(ChunkPlan plan, int nseg,
+                                                           const double* __restrict__ part,
+                                                           float* mass) {
+  const int bh = blockIdx.x, a = blockIdx.y;
   double s = 0.0;
-  for (int c = plan.first[a]; c < plan.first[a + 1]; ++c) s += part[(int64_t)bh * plan.n_chunks + c];
-  mass[(int64_t)bh * nseg + a] = (float)s;
+  for (int c = plan.first[a] + (int)threadIdx.x; c < plan.first[a + 1]; c += 64)
+    s += part[(int64_t)bh * plan.n_chunks + c];
+  s = wave_sum_d(s);
+  if (threadIdx.x == 0) mass[(int64_t)bh * nseg + a] = (float)s;
 }
 
 // Eq. 1 bracket from attention statistics: sum over the query heads of a KV
@@ -451,7 +455,7 @@ hipError_t launch_score_colsum(const uc_shape& sh, const KSegs& segs, const Chun
 
 hipError_t launch_mass_finalize(const ChunkPlan& plan, int BH, int n_segs,
                                 const double* mass_partial, float* mass, hipStream_t st) {
-  hipLaunchKernelGGL(mass_finalize_kernel, dim3(BH), dim3(64), 0, st, plan, n_segs, mass_partial,
+  hipLaunchKernelGGL(mass_finalize_kernel, dim3(BH, n_segs), dim3(64), 0, st, plan, n_segs, mass_partial,
                      mass);
   return hipGetLastError();
 }

@@ -193,6 +193,17 @@ hipError_t launch_attend_generic(const uc_shape& sh, const KSegs& segs, const Ch
 hipError_t launch_attend_combine(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                                  int M, const float* partial, float* o, float* lse, float* seg_lse,
                                  hipStream_t st);
+// binary32 matrix-core kernels (every input outside the bf16 kernels)
+hipError_t launch_attend_wide(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
+                              const void* q, int q_dt, int M, float sm_scale, float* partial,
+                              bool want_o, hipStream_t st);
+hipError_t launch_record_merge(int D, int Q, int C, const float* partial, float* o, float* lse,
+                               hipStream_t st);
+int score_wide_chunk_rows();
+hipError_t launch_score_wide(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
+                             const void* q, int q_dt, int W, int q_ld, float sm_scale,
+                             const float* lse, float* const* scores, double* mass_partial,
+                             hipStream_t st);
 hipError_t launch_score_colsum(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                                const void* q, int q_dt, int W, int q_ld, float sm_scale,
                                const float* lse,
