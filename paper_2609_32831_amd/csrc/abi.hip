@@ -22,15 +22,16 @@ namespace uc {
 bool decode_mfma_eligible(const uc_shape& sh, const KSegs& segs, int q_dt, int M);
 bool score_mfma_eligible(const uc_shape& sh, const KSegs& segs, int q_dt);
 bool prefill_mfma_eligible(const uc_shape& sh, const KSegs& segs, int q_dt, int M);
-size_t prefill_mfma_workspace(const uc_shape& sh, const KSegs& segs);
+size_t prefill_mfma_workspace(const uc_shape& sh, const KSegs& segs, int M);
+size_t prefill_mfma_min_workspace(const uc_shape& sh, const KSegs& segs);
 hipError_t launch_prefill_mfma(const uc_shape& sh, const KSegs& segs, const void* q, int M,
                                float sm_scale, float* o, float* lse, float* seg_lse, void* ws,
-                               hipStream_t st);
+                               size_t ws_bytes, hipStream_t st);
 hipError_t launch_prefill_prepare(const uc_shape& sh, const KSegs& segs, void* ws, hipStream_t st,
                                   void* views_out);
-hipError_t launch_prefill_run(const uc_shape& sh, int n_segs, const void* views, const void* q,
-                              int M, float sm_scale, float* o, float* lse, float* seg_lse,
-                              void* ws, hipStream_t st);
+hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void* views,
+                              const void* q, int M, float sm_scale, float* o, float* lse,
+                              float* seg_lse, void* ws, size_t ws_bytes, hipStream_t st);
 int score_mfma_chunk_rows();
 hipError_t launch_score_lse_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                                  const void* q, int W, float sm_scale, float* partial,
@@ -333,13 +334,16 @@ size_t uc_attend_workspace_size(const uc_shape* shape, const uc_segment* segs, i
   if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(*shape, ks, q_dt, M))
     return decode_mfma_workspace(*shape, ks, M);
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M))
-    return prefill_mfma_workspace(*shape, ks);
+    return prefill_mfma_workspace(*shape, ks, M);
   return attend_ws(*shape, ks, M);
 }
 
-uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
-                          const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
-                          float* lse, float* seg_lse, void* ws, size_t ws_bytes, void* stream) {
+// fit: run in ws_bytes even if the reported size is larger, as long as the
+// call can (multi-query calls then cut their keys into fewer splits)
+static uc_status attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
+                              const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
+                              float* lse, float* seg_lse, void* ws, size_t ws_bytes, bool fit,
+                              void* stream) {
   TimerScope timer;
   KSegs ks;
   uc_status st = check_segments(shape, segs, n_segs, ks);
@@ -358,11 +362,11 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_s
     return launched(launch_decode_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, s));
   }
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M)) {
-    const size_t need = prefill_mfma_workspace(*shape, ks);
+    const size_t need = fit ? prefill_mfma_min_workspace(*shape, ks) : prefill_mfma_workspace(*shape, ks, M);
     if (ws_bytes < need || (need && !ws))
       return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
     g_last_kernel = "prefill_mfma";
-    return launched(launch_prefill_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, s));
+    return launched(launch_prefill_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, ws_bytes, s));
   }
   const ChunkPlan p = attend_plan(*shape, ks, M);
   const size_t need = attend_ws(*shape, ks, M);
@@ -379,6 +383,13 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_s
     e = seg_lse ? launch_attend_combine(*shape, ks, p, M, partial, o, lse, seg_lse, s)
                 : launch_record_merge(shape->D, shape->B * shape->Hq * M, p.n_chunks, partial, o, lse, s);
   return launched(e);
+}
+
+uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
+                          const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
+                          float* lse, float* seg_lse, void* ws, size_t ws_bytes, void* stream) {
+  return attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws, ws_bytes,
+                      false, stream);
 }
 
 // ---------------------------------------------------------------- allocation-free attention
@@ -419,7 +430,9 @@ extern "C" uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_seg
   uc_status st = check_segments(shape, segs, n_segs, ks);
   if (st) return st;
   if (M < 1 || !dtype_ok(q_dt)) return fail(UC_E_INVALID, "bad M (%d) or q dtype (%d)", M, q_dt);
-  const size_t need = uc_attend_workspace_size(shape, segs, n_segs, q_dt, M);
+  const bool prefill = g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M);
+  const size_t need = prefill ? prefill_mfma_min_workspace(*shape, ks)
+                              : uc_attend_workspace_size(shape, segs, n_segs, q_dt, M);
   if (need > UC_SCRATCH_BYTES)
     return fail(UC_E_UNSUPPORTED,
                 "this call needs %zu bytes of scratch, above the %u-byte static array; use "
@@ -427,8 +440,8 @@ extern "C" uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_seg
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st) return st;
-  return uc_attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws,
-                         UC_SCRATCH_BYTES, stream);
+  return attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws,
+                      UC_SCRATCH_BYTES, true, stream);
 }
 
 // ---------------------------------------------------------------- decode step, append fused
@@ -557,7 +570,7 @@ uc_status uc_plan_create(const uc_shape* shape, const uc_segment* segs, int n_se
   check_segments(shape, full, n_segs, kf);
   size_t need;
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, kf, q_dt, M)) {
-    need = prefill_mfma_workspace(*shape, kf);
+    need = prefill_mfma_workspace(*shape, kf, M);
   } else {
     need = attend_ws(*shape, kf, M);
     if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(*shape, kf, q_dt, M))
@@ -600,8 +613,8 @@ uc_status uc_plan_attend(uc_plan plan, const void* q, float* o, float* lse, floa
     plan->prepared_ws = ws;
   }
   g_last_kernel = "prefill_mfma";
-  return launched(launch_prefill_run(sh, plan->n_segs, plan->views, q, plan->M, plan->sm_scale, o,
-                                     lse, seg_lse, ws, s));
+  return launched(launch_prefill_run(sh, plan->ks, plan->views, q, plan->M, plan->sm_scale, o, lse,
+                                     seg_lse, ws, ws_bytes, s));
 }
 
 uc_status uc_plan_attend_append(uc_plan plan, const void* k_new, const void* v_new, int n_new,

@@ -27,11 +27,11 @@
 // tiles alternate between two register sets.  The rare raise of the reference
 // maximum runs
 // after the matrix instructions (it rescales the accumulators they update).
-// Outputs (normalised O, lse, per-segment lse) are written directly; no
-// split over keys.  Workgroups are mapped so that those of one (b, h_kv) run
+// Outputs (normalised O, lse, per-segment lse) are written directly; only a
+// call with too few query blocks for the chip splits the keys (Split).  Workgroups are mapped so that those of one (b, h_kv) run
 // on the same XCD and share its L2 copy of the head's rows.
 //
-// Packed segments first go through dequant_kernel: codes -> round_to_bf16(
+// Packed segments first go through prepare_kernel: codes -> round_to_bf16(
 // fmaf(code, scale, min)) into a [B, Hkv, n_full, D] bf16 workspace (once per
 // call, where the query blocks of a head would otherwise each decode every
 // packed tile again); their residual tails are read in place.  This
@@ -39,6 +39,7 @@
 // own, so an execution plan over an unchanged cache runs it once.
 #include <string.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "mfma_util.h"
@@ -61,6 +62,7 @@ constexpr int qrows() { return W * QT * 16; }
 constexpr float kLazy = 8.0f;
 constexpr float kLazyExp = 256.0f;  // 2^kLazy
 constexpr int kMaxViews = 2 * kMaxSeg;
+constexpr int kPrepBlocks = 256, kPrepThreads = 1024;  // of prepare_kernel; one flag byte per block
 
 // dense row views of the logical sequence, in order; seg = logical segment
 struct View {
@@ -76,6 +78,18 @@ struct Views {
   View v[kMaxViews];
   int n;
   int tiles;  // total key tiles
+};
+
+// A call whose query blocks leave CUs idle splits its key tiles: split s of a
+// query block takes tiles [s*per, (s+1)*per) and leaves an unnormalised
+// record of every query row -- (m, l) in base 2, O, and the log-sum-exp of
+// each segment's rows it saw -- for split_merge_kernel.  Record s of query
+// row r is number r*n + s.  n = 1: outputs are written directly.
+struct Split {
+  int n, per;
+  float* ml;
+  float* o;
+  float* seg;
 };
 
 struct QState {
@@ -351,15 +365,16 @@ __device__ __attribute__((always_inline)) inline void tile_step(
   }
 }
 
-// the key-tile loop of one workgroup (see the file comment).  Returns the
-// view of the last tile.
-template <bool F16, int W, int TPS, int QT>
+// the key-tile loop of one workgroup over all tiles or those of its key split
+// (see the file comment).  Returns the view of the last tile.
+template <bool F16, int W, int TPS, int QT, bool SPLIT>
 __device__ __attribute__((always_inline)) inline int tile_loop(
-    const Views& vs, int bh, char* lds, const u4 (&qop)[QT][4], QState (&st)[QT],
-    float scale_log2, int r_wave, int nq, int64_t qbase, int nseg, float* seg_lse, int i16,
-    int g4) {
+    const Views& vs, const Split& sp, int split, int bh, char* lds, const u4 (&qop)[QT][4],
+    QState (&st)[QT], float scale_log2, int r_wave, int nq, int64_t qbase, int nseg,
+    float* seg_lse, int i16, int g4) {
   int cur_view = -1, cur_seg = -1;
-  const int T = vs.tiles;
+  const int t_first = SPLIT ? split * sp.per : 0;
+  const int T = SPLIT ? min(sp.per, vs.tiles - t_first) : vs.tiles;
   // tiles go through LDS in stages of TPS: stage j holds tiles TPS*j ..
   // TPS*j + TPS - 1; after the last tile of stage j the tiles of stage j + 2
   // are stored, and one barrier per stage publishes them.  During stage j
@@ -372,8 +387,8 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
   Stage SA, SB;
   {
     Stage S;
-    ct.start(vs, bh, 0);
-    cs.start(vs, bh, 0);
+    ct.start(vs, bh, t_first);
+    cs.start(vs, bh, t_first);
     for (int u = 0; u < 2 * TPS && u < T; ++u) {
       // the chunks of tile u (both with one tile per stage)
 #pragma unroll
@@ -428,7 +443,7 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
         const float ls = col_sum(st[qt].ls);
         const int r = r_wave + qt * 16 + i16;
         if (g4 == 0 && r < nq)
-          seg_lse[(qbase + r) * nseg + cur_seg] =
+          seg_lse[(SPLIT ? (qbase + r) * sp.n + split : qbase + r) * nseg + cur_seg] =
               ls > 0.0f ? (st[qt].m + __log2f(ls)) * kLn2 : -INFINITY;
         st[qt].ls = 0.0f;
       }
@@ -473,21 +488,24 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
   return cur_view;
 }
 
-template <int W, int TPS, int QT>
+template <int W, int TPS, int QT, bool SPLIT>
 __global__ __launch_bounds__(W * 64, W == 4 && QT == 2 ? 2 : 1) void prefill_mfma_kernel(Views vs, const uint16_t* __restrict__ q,
                                                               int Hq, int Hkv, int M, int nseg,
                                                               int n_qblocks, int n_work,
                                                               float scale_log2, float* __restrict__ o,
                                                               float* __restrict__ lse,
                                                               float* __restrict__ seg_lse,
-                                                              const int* __restrict__ v_unsafe) {
+                                                              Split sp,
+                                                              const uint32_t* __restrict__ flags) {
   __shared__ __attribute__((aligned(16))) char lds[STAGES * TPS * SUBB];
   // XCD-aware work mapping: consecutive work items (the query blocks of one
   // head, which share its K/V rows) go to the same XCD
   const int per_xcd = (n_work + 7) / 8;
   const int work = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (work >= n_work) return;
-  const int qb = work % n_qblocks, bh = work / n_qblocks;
+  // the query blocks of one key split of one head are consecutive
+  const int qb = work % n_qblocks, hs = work / n_qblocks;
+  const int split = SPLIT ? hs % sp.n : 0, bh = SPLIT ? hs / sp.n : hs;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i16 = lane & 15, g4 = lane >> 4;
   const int G = Hq / Hkv, nq = G * M, b = bh / Hkv, hkv = bh % Hkv;
@@ -516,14 +534,21 @@ __global__ __launch_bounds__(W * 64, W == 4 && QT == 2 ? 2 : 1) void prefill_mfm
     for (int t = 0; t < QT; ++t) {
       const int r = r_wave + t * 16 + i16;
       if (r < nq)
-        for (int a = 0; a < nseg; ++a) seg_lse[(qbase + r) * nseg + a] = -INFINITY;
+        for (int a = 0; a < nseg; ++a)
+          seg_lse[(SPLIT ? (qbase + r) * sp.n + split : qbase + r) * nseg + a] = -INFINITY;
     }
   }
-  const bool f16 = *v_unsafe == 0;
-  const int cur_view = f16 ? tile_loop<true, W, TPS, QT>(vs, bh, lds, qop, st, scale_log2, r_wave, nq, qbase,
-                                             nseg, seg_lse, i16, g4)
-                           : tile_loop<false, W, TPS, QT>(vs, bh, lds, qop, st, scale_log2, r_wave, nq, qbase,
-                                              nseg, seg_lse, i16, g4);
+  // did any workgroup of the preparation meet a V value outside fp16's range
+  // (scalar loads: the flags as a vector register cost the tile loop 3 %)
+  uint32_t unsafe_v = 0;
+#pragma unroll
+  for (int i = 0; i < kPrepBlocks / 4; ++i) unsafe_v |= flags[i];
+  const bool f16 = unsafe_v == 0;
+  const int cur_view =
+      f16 ? tile_loop<true, W, TPS, QT, SPLIT>(vs, sp, split, bh, lds, qop, st, scale_log2, r_wave,
+                                               nq, qbase, nseg, seg_lse, i16, g4)
+          : tile_loop<false, W, TPS, QT, SPLIT>(vs, sp, split, bh, lds, qop, st, scale_log2, r_wave,
+                                                nq, qbase, nseg, seg_lse, i16, g4);
   // outputs
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
@@ -531,102 +556,172 @@ __global__ __launch_bounds__(W * 64, W == 4 && QT == 2 ? 2 : 1) void prefill_mfm
     const float l = col_sum(st[qt].l);
     const float ls = col_sum(st[qt].ls);
     if (r < nq) {
-      const float inv = 1.0f / l;
-      float* orow = o + (qbase + r) * D;
+      const int64_t rec = SPLIT ? (qbase + r) * sp.n + split : qbase + r;
+      const float inv = SPLIT ? 1.0f : 1.0f / l;
+      float* orow = (SPLIT ? sp.o : o) + rec * D;
 #pragma unroll
       for (int d = 0; d < 8; ++d) *reinterpret_cast<f4*>(orow + d * 16 + g4 * 4) = st[qt].acc[d] * inv;
       if (g4 == 0) {
-        if (lse) lse[qbase + r] = (st[qt].m + __log2f(l)) * kLn2;
+        if (SPLIT) *reinterpret_cast<f2*>(sp.ml + rec * 2) = f2{st[qt].m, l};
+        else if (lse) lse[rec] = (st[qt].m + __log2f(l)) * kLn2;
         if (seg_lse && cur_view >= 0)
-          seg_lse[(qbase + r) * nseg + vs.v[cur_view].seg] =
+          seg_lse[rec * nseg + vs.v[cur_view].seg] =
               ls > 0.0f ? (st[qt].m + __log2f(ls)) * kLn2 : -INFINITY;
       }
     }
   }
 }
 
-// codes -> bf16 values of one packed segment's whole row groups:
-// out[b, h, r, c] = round_to_bf16(fmaf(code, scale, min)); one thread per
-// 8 channels of one row, K and V: the 8 codes in one 16-, 32- or 64-bit load,
-// the key scales and minima in 16-byte loads, one value group (groups are at
-// least 8 channels)
-__global__ void dequant_kernel(KSeg s, int BH, uint16_t* __restrict__ kout,
-                               uint16_t* __restrict__ vout, uint16_t* __restrict__ vhout,
-                               int* __restrict__ v_unsafe) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // (bh, row, c8)
-  const int c8 = (int)(e % (D / 8));
-  const int64_t rr = e / (D / 8);
-  const int r = (int)(rr % s.n_full), bh = (int)(rr / s.n_full);
-  if (bh >= BH) return;
+// One wave per query row: its n records merged into O (each lane two dims),
+// lse and the per-segment lse.  Eight records are loaded at a time, all before
+// any is used; every record holds at least one key tile, so its m is finite.
+__global__ __launch_bounds__(256) void split_merge_kernel(int Q, int n, int nseg, Split sp,
+                                                          float* __restrict__ o,
+                                                          float* __restrict__ lse,
+                                                          float* __restrict__ seg_lse) {
+  const int64_t qi = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (qi >= Q) return;
+  const int lane = threadIdx.x & 63;
+  const float* ml = sp.ml + qi * n * 2;
+  const float* po = sp.o + qi * n * D + 2 * lane;
+  float M = -INFINITY, l = 0.0f;
+  f2 acc = f2{0.0f, 0.0f};
+  for (int s0 = 0; s0 < n; s0 += 8) {
+    f2 a[8], x[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int s = min(s0 + r, n - 1);
+      a[r] = *reinterpret_cast<const f2*>(ml + 2 * s);
+      x[r] = *reinterpret_cast<const f2*>(po + (int64_t)s * D);
+    }
+    float mx = M;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) mx = fmaxf(mx, a[r][0]);
+    const float c = __builtin_amdgcn_exp2f(M - mx);
+    l *= c;
+    acc *= c;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float w = s0 + r < n ? __builtin_amdgcn_exp2f(a[r][0] - mx) : 0.0f;
+      l = fmaf(w, a[r][1], l);
+      acc[0] = fmaf(w, x[r][0], acc[0]);
+      acc[1] = fmaf(w, x[r][1], acc[1]);
+    }
+    M = mx;
+  }
+  *reinterpret_cast<f2*>(o + qi * D + 2 * lane) = acc * (1.0f / l);
+  if (lse && lane == 0) lse[qi] = (M + log2f(l)) * kLn2;
+  if (seg_lse && lane < nseg) {
+    const float* ps = sp.seg + qi * n * nseg + lane;
+    float m = -INFINITY, t = 0.0f;
+    for (int s = 0; s < n; ++s) m = fmaxf(m, ps[s * nseg]);
+    if (m != -INFINITY)
+      for (int s = 0; s < n; ++s) t += expf(ps[s * nseg] - m);
+    seg_lse[qi * nseg + lane] = m == -INFINITY ? m : m + logf(t);
+  }
+}
+
+// 8 channels (column chunk c8) of row r of head bh of a packed segment:
+// round_to_bf16(fmaf(code, scale, min)), the 8 codes in one 16-, 32- or
+// 64-bit load, the key scales and minima in 16-byte loads, one value group
+// (groups are at least 8 channels)
+__device__ inline void dequant8(const KSeg& s, int bh, int r, int c8, u4& ko, u4& vo) {
   int bits;
   int64_t off;
-  u4 ko, vo;
   if (!head_codes(s, bh, D, bits, off) || (off & 15)) {
     const uint32_t nan2 = 0x7FC07FC0u;
     ko = u4{nan2, nan2, nan2, nan2};
     vo = ko;
-  } else {
-    const int rb = D * bits / 8, G = s.group;
-    const int64_t cb = off + (int64_t)r * rb + c8 * bits;  // 8 channels = bits bytes
-    uint64_t wk, wv;
-    if (bits == 4) {
-      wk = *reinterpret_cast<const uint32_t*>(s.codes_k + cb);
-      wv = *reinterpret_cast<const uint32_t*>(s.codes_v + cb);
-    } else if (bits == 2) {
-      wk = *reinterpret_cast<const uint16_t*>(s.codes_k + cb);
-      wv = *reinterpret_cast<const uint16_t*>(s.codes_v + cb);
-    } else {
-      wk = *reinterpret_cast<const uint64_t*>(s.codes_k + cb);
-      wv = *reinterpret_cast<const uint64_t*>(s.codes_v + cb);
-    }
-    const int mask = (1 << bits) - 1;
-    const int64_t kg = ((int64_t)bh * s.kgroups + r / G) * D + c8 * 8;
-    const f4 sk0 = *reinterpret_cast<const f4*>(s.scale_k + kg);
-    const f4 sk1 = *reinterpret_cast<const f4*>(s.scale_k + kg + 4);
-    const f4 mk0 = *reinterpret_cast<const f4*>(s.min_k + kg);
-    const f4 mk1 = *reinterpret_cast<const f4*>(s.min_k + kg + 4);
-    const float sk[8] = {sk0[0], sk0[1], sk0[2], sk0[3], sk1[0], sk1[1], sk1[2], sk1[3]};
-    const float mk[8] = {mk0[0], mk0[1], mk0[2], mk0[3], mk1[0], mk1[1], mk1[2], mk1[3]};
-    const int64_t vi = ((int64_t)bh * s.cap_full + r) * (D / G) + (c8 * 8) / G;
-    const float sv = s.scale_v[vi], mv = s.min_v[vi];
-    uint32_t kw[4], vw[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c0 = 2 * j, c1 = 2 * j + 1;
-      const float k0 = fmaf((float)((wk >> (c0 * bits)) & mask), sk[c0], mk[c0]);
-      const float k1 = fmaf((float)((wk >> (c1 * bits)) & mask), sk[c1], mk[c1]);
-      const float v0 = fmaf((float)((wv >> (c0 * bits)) & mask), sv, mv);
-      const float v1 = fmaf((float)((wv >> (c1 * bits)) & mask), sv, mv);
-      kw[j] = bf2(k0, k1);
-      vw[j] = bf2(v0, v1);
-    }
-    ko = u4{kw[0], kw[1], kw[2], kw[3]};
-    vo = u4{vw[0], vw[1], vw[2], vw[3]};
+    return;
   }
-  const int64_t oi = ((int64_t)bh * s.n_full + r) * D + c8 * 8;
-  *reinterpret_cast<u4*>(kout + oi) = ko;
-  *reinterpret_cast<u4*>(vout + oi) = vo;
-  *reinterpret_cast<u4*>(vhout + oi) =
-      u4{bf2_to_h2(vo[0]), bf2_to_h2(vo[1]), bf2_to_h2(vo[2]), bf2_to_h2(vo[3])};
-  if (bf2_over_f16(vo[0]) || bf2_over_f16(vo[1]) || bf2_over_f16(vo[2]) || bf2_over_f16(vo[3]))
-    atomicOr(v_unsafe, 1);
+  const int rb = D * bits / 8, lgG = __builtin_ctz((unsigned)s.group);
+  const int64_t cb = off + (int64_t)r * rb + c8 * bits;  // 8 channels = bits bytes
+  uint64_t wk, wv;
+  if (bits == 4) {
+    wk = *reinterpret_cast<const uint32_t*>(s.codes_k + cb);
+    wv = *reinterpret_cast<const uint32_t*>(s.codes_v + cb);
+  } else if (bits == 2) {
+    wk = *reinterpret_cast<const uint16_t*>(s.codes_k + cb);
+    wv = *reinterpret_cast<const uint16_t*>(s.codes_v + cb);
+  } else {
+    wk = *reinterpret_cast<const uint64_t*>(s.codes_k + cb);
+    wv = *reinterpret_cast<const uint64_t*>(s.codes_v + cb);
+  }
+  const int mask = (1 << bits) - 1;
+  const int64_t kg = ((int64_t)bh * s.kgroups + (r >> lgG)) * D + c8 * 8;
+  const f4 sk0 = *reinterpret_cast<const f4*>(s.scale_k + kg);
+  const f4 sk1 = *reinterpret_cast<const f4*>(s.scale_k + kg + 4);
+  const f4 mk0 = *reinterpret_cast<const f4*>(s.min_k + kg);
+  const f4 mk1 = *reinterpret_cast<const f4*>(s.min_k + kg + 4);
+  const float sk[8] = {sk0[0], sk0[1], sk0[2], sk0[3], sk1[0], sk1[1], sk1[2], sk1[3]};
+  const float mk[8] = {mk0[0], mk0[1], mk0[2], mk0[3], mk1[0], mk1[1], mk1[2], mk1[3]};
+  const int64_t vi = ((int64_t)bh * s.cap_full + r) * (D >> lgG) + ((c8 * 8) >> lgG);
+  const float sv = s.scale_v[vi], mv = s.min_v[vi];
+  uint32_t kw[4], vw[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int c0 = 2 * j, c1 = 2 * j + 1;
+    const float k0 = fmaf((float)((wk >> (c0 * bits)) & mask), sk[c0], mk[c0]);
+    const float k1 = fmaf((float)((wk >> (c1 * bits)) & mask), sk[c1], mk[c1]);
+    const float v0 = fmaf((float)((wv >> (c0 * bits)) & mask), sv, mv);
+    const float v1 = fmaf((float)((wv >> (c1 * bits)) & mask), sv, mv);
+    kw[j] = bf2(k0, k1);
+    vw[j] = bf2(v0, v1);
+  }
+  ko = u4{kw[0], kw[1], kw[2], kw[3]};
+  vo = u4{vw[0], vw[1], vw[2], vw[3]};
 }
 
-// V rows of a dense view: flag values that fp16 cannot hold
-// fp16 copy of a view's bf16 V rows ([BH, n, D], round to nearest even) and
-// the range check: a value with no fp16 counterpart sets the flag
-__global__ void vconvert_kernel(const uint16_t* __restrict__ v, int64_t bh_stride, int n_rows,
-                                uint16_t* __restrict__ vh, int* __restrict__ v_unsafe) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // 8 elements each
-  if (e >= (int64_t)n_rows * (D / 8)) return;
-  const u4 x = *reinterpret_cast<const u4*>(v + blockIdx.y * bh_stride + e * 8);
-  *reinterpret_cast<u4*>(vh + (int64_t)blockIdx.y * n_rows * D + e * 8) =
-      u4{bf2_to_h2(x[0]), bf2_to_h2(x[1]), bf2_to_h2(x[2]), bf2_to_h2(x[3])};
-  if (bf2_over_f16(x[0]) || bf2_over_f16(x[1]) || bf2_over_f16(x[2]) || bf2_over_f16(x[3]))
-    atomicOr(v_unsafe, 1);
-}
+// Preparation of a call in one launch: for every view, either the dequantised
+// rows of a packed segment (bf16 K and V, fp16 V) or the fp16 copy of a dense
+// view's V rows (round to nearest even).  A workgroup that meets a V value
+// with no fp16 counterpart says so in its own flag byte, which the attention
+// kernel reads, so no flag has to be cleared by a launch before this one.
+// (A clearing kernel, a dequantisation and one conversion per dense view were
+// four launches of 2 to 8 us each for a prompt of 203 rows over 6144; this one
+// takes 8 us.  Two items per thread and pass: 11 us.)
+struct PrepView {
+  const uint16_t* src;  // dense: V rows of (b, h_kv) 0; packed: NULL
+  uint16_t *kd, *vd;    // packed: dequantised rows
+  uint16_t* vh;
+  int64_t bh_stride;    // dense: elements between heads of src
+  int n, seg;           // rows per head, segment (packed)
+};
+struct Prep {
+  PrepView v[kMaxViews];
+  int n, BH;
+};
 
-__global__ void flag_clear_kernel(int* flag) { *flag = 0; }
+__global__ __launch_bounds__(kPrepThreads) void prepare_kernel(KSegs segs, Prep p,
+                                                               uint8_t* __restrict__ flags) {
+  bool over = false;
+  for (int i = 0; i < p.n; ++i) {
+    const PrepView& w = p.v[i];
+    const int64_t items = (int64_t)p.BH * w.n * (D / 8);
+    for (int64_t e = (int64_t)blockIdx.x * kPrepThreads + threadIdx.x; e < items;
+         e += (int64_t)kPrepBlocks * kPrepThreads) {
+      const uint32_t rr = (uint32_t)(e / (D / 8));  // fewer than 2^32 rows fit any memory
+      const int c8 = (int)(e % (D / 8));
+      const uint32_t bh = rr / (uint32_t)w.n, r = rr % (uint32_t)w.n;
+      const int64_t oi = (int64_t)rr * D + c8 * 8;
+      u4 vo;
+      if (w.src) {
+        vo = *reinterpret_cast<const u4*>(w.src + bh * w.bh_stride + (int64_t)r * D + c8 * 8);
+      } else {
+        u4 ko;
+        dequant8(segs.s[w.seg], (int)bh, (int)r, c8, ko, vo);
+        *reinterpret_cast<u4*>(w.kd + oi) = ko;
+        *reinterpret_cast<u4*>(w.vd + oi) = vo;
+      }
+      *reinterpret_cast<u4*>(w.vh + oi) =
+          u4{bf2_to_h2(vo[0]), bf2_to_h2(vo[1]), bf2_to_h2(vo[2]), bf2_to_h2(vo[3])};
+      over = over || bf2_over_f16(vo[0]) || bf2_over_f16(vo[1]) || bf2_over_f16(vo[2]) ||
+             bf2_over_f16(vo[3]);
+    }
+  }
+  const int any = __syncthreads_or(over);
+  if (threadIdx.x == 0) flags[blockIdx.x] = any != 0;
+}
 
 }  // namespace
 
@@ -638,28 +733,64 @@ bool prefill_mfma_eligible(const uc_shape& sh, const KSegs& segs, int q_dt, int 
   return true;
 }
 
-// Workspace: a flag word (some V value outside fp16's range), then bf16 K
+// Key splits of a call: none when its query blocks fill half of the resident
+// workgroups (two per CU of the four-wave layout), else as many as fill them,
+// each of at least kSplitTiles key tiles.  The count never falls as rows are
+// added.  Measured, 203 query rows of 28 heads on 4 KV heads over 6144 rows (48
+// query blocks), attention kernel alone: 148 us unsplit, 45 with 5 splits, 42
+// with 8, 38 with 10 (the rule), 42 with 16.  Grids that already fill the chip
+// lose: 1792 query blocks (3.5 rounds) 760 us unsplit, 1133 with 16.
+constexpr int kSplitTiles = 8, kMaxSplits = 16;
+
+static int64_t narrow_blocks(const uc_shape& sh, int M) {
+  const int64_t nq = (int64_t)(sh.Hq / sh.Hkv) * M;
+  return (nq + qrows<4, 2>() - 1) / qrows<4, 2>() * sh.B * sh.Hkv;
+}
+
+static int prefill_splits(const uc_shape& sh, int tiles, int M) {
+  const int64_t blocks = narrow_blocks(sh, M);
+  const int64_t n = std::min<int64_t>({2 * device_cus() / blocks, tiles / kSplitTiles, kMaxSplits});
+  return (int)std::max<int64_t>(n, 1);
+}
+
+static size_t split_bytes(const uc_shape& sh, int M, int n_segs) {  // of one split
+  return (size_t)sh.B * sh.Hq * M * (D + 2 + n_segs) * sizeof(float);
+}
+
+static size_t round256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Workspace: the preparation's flags (one byte per workgroup), then bf16 K
 // and V plus fp16 V of every packed segment's whole row groups, and the fp16
-// V copy of every dense view (dense segments, residual tails).
-size_t prefill_mfma_workspace(const uc_shape& sh, const KSegs& segs) {
+// V copy of every dense view (dense segments, residual tails); then the
+// records of the key splits.  A call runs with the first part alone
+// (unsplit); the size reported to callers holds the records too.
+size_t prefill_mfma_min_workspace(const uc_shape& sh, const KSegs& segs) {
   const size_t BH = (size_t)sh.B * sh.Hkv;
-  auto round = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  size_t bytes = 256;
+  size_t bytes = kPrepBlocks;
   for (int i = 0; i < segs.n; ++i) {
     const KSeg& s = segs.s[i];
     if (s.kind == UC_SEG_PACKED) {
-      bytes += round(BH * s.n_full * D * 2 * 3);
-      bytes += round(BH * s.tail_len * D * 2);
+      bytes += round256(BH * s.n_full * D * 2 * 3);
+      bytes += round256(BH * s.tail_len * D * 2);
     } else {
-      bytes += round(BH * s.n_rows * D * 2);
+      bytes += round256(BH * s.n_rows * D * 2);
     }
   }
   return bytes;
 }
 
+size_t prefill_mfma_workspace(const uc_shape& sh, const KSegs& segs, int M) {
+  // tiles: every view rounds up, so one more than a segment's rows give
+  // bounds it, and the bound grows with the rows
+  int64_t tiles = 0;
+  for (int i = 0; i < segs.n; ++i) tiles += segs.s[i].n_rows / TILE + 2;
+  const int n = prefill_splits(sh, (int)std::min<int64_t>(tiles, INT32_MAX), M);
+  return prefill_mfma_min_workspace(sh, segs) + (n > 1 ? round256(n * split_bytes(sh, M, segs.n)) : 0);
+}
+
 static_assert(sizeof(Views) <= kPrefillViewBytes, "prepared views do not fit their slot");
 
-// Preparation of a call: the range flag, the dequantised rows of every
+// Preparation of a call: the range flags, the dequantised rows of every
 // packed segment and the fp16 V copies, all in ws; the views the attention
 // kernel walks go to views_out (kPrefillViewBytes).  The result depends only
 // on the segments' contents and ws, so calls over unchanged segments can
@@ -668,65 +799,52 @@ hipError_t launch_prefill_prepare(const uc_shape& sh, const KSegs& segs, void* w
                                   void* views_out) {
   const int BH = sh.B * sh.Hkv;
   Views vs{};
-  int* v_unsafe = (int*)ws;
-  char* wp = (char*)ws + 256;
-  int tiles = 0;
-  // the PV product runs in fp16 when every V value fits fp16 (checked here,
-  // decided in the kernel); otherwise in bf16 hi + lo parts
-  hipLaunchKernelGGL(flag_clear_kernel, dim3(1), dim3(1), 0, st, v_unsafe);
+  Prep pr{};
+  pr.BH = BH;
+  char* wp = (char*)ws + kPrepBlocks;
+  auto take = [&](size_t bytes) {
+    char* p = wp;
+    wp += round256(bytes);
+    return (uint16_t*)p;
+  };
+  // views without rows are left out (their tiles would be empty)
+  auto add = [&](const View& v, uint16_t* kd, uint16_t* vd) {
+    if (v.n == 0) return;
+    pr.v[vs.n] = PrepView{kd ? nullptr : v.v, kd, vd, (uint16_t*)v.vh, v.bh_stride, v.n, v.seg};
+    vs.v[vs.n++] = v;
+    vs.tiles += (v.n + TILE - 1) / TILE;
+  };
   for (int i = 0; i < segs.n; ++i) {
     const KSeg& s = segs.s[i];
-    auto take = [&](size_t bytes) {
-      char* p = wp;
-      wp += (bytes + 255) & ~(size_t)255;
-      return (uint16_t*)p;
-    };
     if (s.kind == UC_SEG_DENSE) {
-      vs.v[vs.n++] = View{(const uint16_t*)s.k, (const uint16_t*)s.v,
-                          take((size_t)BH * s.n_rows * D * 2), (int64_t)s.row_stride * D, s.n_rows, i};
+      add(View{(const uint16_t*)s.k, (const uint16_t*)s.v, take((size_t)BH * s.n_rows * D * 2),
+               (int64_t)s.row_stride * D, s.n_rows, i}, nullptr, nullptr);
       continue;
     }
-    if (s.n_full > 0) {
-      uint16_t* kd = take((size_t)BH * s.n_full * D * 2 * 3);
-      uint16_t* vd = kd + (size_t)BH * s.n_full * D;
-      uint16_t* vh = vd + (size_t)BH * s.n_full * D;
-      const int64_t n_thr = (int64_t)BH * s.n_full * (D / 8);
-      hipLaunchKernelGGL(dequant_kernel, dim3((unsigned)((n_thr + 255) / 256)), dim3(256), 0, st,
-                         s, BH, kd, vd, vh, v_unsafe);
-      vs.v[vs.n++] = View{kd, vd, vh, (int64_t)s.n_full * D, s.n_full, i};
-    }
+    const size_t head = (size_t)BH * s.n_full * D;
+    uint16_t* kd = take(head * 2 * 3);
+    add(View{kd, kd + head, kd + 2 * head, (int64_t)s.n_full * D, s.n_full, i}, kd, kd + head);
     uint16_t* th = take((size_t)BH * s.tail_len * D * 2);
-    if (s.tail_len > 0)
-      vs.v[vs.n++] = View{(const uint16_t*)s.tail_k, (const uint16_t*)s.tail_v, th,
-                          (int64_t)s.tail_stride * D, s.tail_len, i};
+    add(View{(const uint16_t*)s.tail_k, (const uint16_t*)s.tail_v, th, (int64_t)s.tail_stride * D,
+             s.tail_len, i}, nullptr, nullptr);
   }
-  // drop empty views (their tiles would be empty); keep the order
-  int n = 0;
-  for (int i = 0; i < vs.n; ++i)
-    if (vs.v[i].n > 0) vs.v[n++] = vs.v[i];
-  vs.n = n;
-  for (int i = 0; i < n; ++i) {
-    tiles += (vs.v[i].n + TILE - 1) / TILE;
-    if (segs.s[vs.v[i].seg].kind == UC_SEG_PACKED && vs.v[i].v != (const uint16_t*)segs.s[vs.v[i].seg].tail_v)
-      continue;  // dequantised rows were converted and checked by the dequant kernel
-    const int64_t per = (int64_t)vs.v[i].n * (D / 8);
-    hipLaunchKernelGGL(vconvert_kernel, dim3((unsigned)((per + 255) / 256), BH), dim3(256), 0, st,
-                       vs.v[i].v, vs.v[i].bh_stride, vs.v[i].n, (uint16_t*)vs.v[i].vh, v_unsafe);
-  }
-  vs.tiles = tiles;
+  pr.n = vs.n;
+  hipLaunchKernelGGL(prepare_kernel, dim3(kPrepBlocks), dim3(kPrepThreads), 0, st, segs, pr,
+                     (uint8_t*)ws);
   memcpy(views_out, &vs, sizeof vs);
   return hipGetLastError();
 }
 
 // The attention kernel over prepared views (launch_prefill_prepare on the
-// same ws).
-hipError_t launch_prefill_run(const uc_shape& sh, int n_segs, const void* views, const void* q,
-                              int M, float sm_scale, float* o, float* lse, float* seg_lse,
-                              void* ws, hipStream_t st) {
+// same ws).  ws_bytes: at least prefill_mfma_min_workspace; the key splits
+// take what is there beyond it.
+hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void* views,
+                              const void* q, int M, float sm_scale, float* o, float* lse,
+                              float* seg_lse, void* ws, size_t ws_bytes, hipStream_t st) {
   Views vs;
   memcpy(&vs, views, sizeof vs);
-  const int BH = sh.B * sh.Hkv;
-  const int* v_unsafe = (const int*)ws;
+  const int BH = sh.B * sh.Hkv, n_segs = segs.n;
+  const uint32_t* flags = (const uint32_t*)ws;
   hipError_t e;
   const int nq = (sh.Hq / sh.Hkv) * M;
   // the 8-wave layout (one workgroup per CU) when its grid fills every round
@@ -737,28 +855,49 @@ hipError_t launch_prefill_run(const uc_shape& sh, int n_segs, const void* views,
   const bool wide = n8 % cus == 0 || n8 >= 8 * cus;
   const int qr = wide ? qrows<8, 2>() : qrows<4, 2>();
   const int n_qblocks = (nq + qr - 1) / qr;
-  const int n_work = n_qblocks * BH;
+  Split sp{1, vs.tiles, nullptr, nullptr, nullptr};
+  if (!wide) {
+    const size_t min = prefill_mfma_min_workspace(sh, segs);
+    const size_t room = (ws_bytes - min) / split_bytes(sh, M, n_segs);
+    const int n = (int)std::min<size_t>(prefill_splits(sh, vs.tiles, M), room);
+    if (n > 1) {
+      sp.per = (vs.tiles + n - 1) / n;
+      sp.n = (vs.tiles + sp.per - 1) / sp.per;
+      const int64_t recs = (int64_t)sh.B * sh.Hq * M * sp.n;
+      sp.o = (float*)((char*)ws + min);
+      sp.ml = sp.o + recs * D;
+      sp.seg = sp.ml + recs * 2;
+    }
+  }
+  const int n_work = n_qblocks * BH * sp.n;
   const int grid = (n_work + 7) / 8 * 8;
   const float sl2 = sm_scale * kLog2e;
   const uint16_t* qp = (const uint16_t*)q;
+  float* seg = sp.n > 1 && seg_lse ? sp.seg : seg_lse;
   if ((e = kernel_timer_begin(st)) != hipSuccess) return e;
-  if (wide)
-    hipLaunchKernelGGL((prefill_mfma_kernel<8, 2, 2>), dim3(grid), dim3(8 * 64), 0, st, vs, qp,
-                       sh.Hq, sh.Hkv, M, n_segs, n_qblocks, n_work, sl2, o, lse, seg_lse, v_unsafe);
-  else
-    hipLaunchKernelGGL((prefill_mfma_kernel<4, 1, 2>), dim3(grid), dim3(4 * 64), 0, st, vs, qp,
-                       sh.Hq, sh.Hkv, M, n_segs, n_qblocks, n_work, sl2, o, lse, seg_lse, v_unsafe);
+  auto go = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * 64), 0, st, vs, qp, sh.Hq, sh.Hkv, M, n_segs,
+                       n_qblocks, n_work, sl2, o, lse, seg, sp, flags);
+  };
+  if (wide) go(prefill_mfma_kernel<8, 2, 2, false>, 8);
+  else if (sp.n == 1) go(prefill_mfma_kernel<4, 1, 2, false>, 4);
+  else go(prefill_mfma_kernel<4, 1, 2, true>, 4);
   e = hipGetLastError();
-  return e == hipSuccess ? kernel_timer_end(st) : e;
+  if (e == hipSuccess) e = kernel_timer_end(st);
+  if (e != hipSuccess || sp.n == 1) return e;
+  const int Q = sh.B * sh.Hq * M;
+  hipLaunchKernelGGL(split_merge_kernel, dim3((Q + 3) / 4), dim3(256), 0, st, Q, sp.n, n_segs, sp, o,
+                     lse, seg_lse);
+  return hipGetLastError();
 }
 
 hipError_t launch_prefill_mfma(const uc_shape& sh, const KSegs& segs, const void* q, int M,
                                float sm_scale, float* o, float* lse, float* seg_lse, void* ws,
-                               hipStream_t st) {
+                               size_t ws_bytes, hipStream_t st) {
   alignas(16) char views[kPrefillViewBytes];
   const hipError_t e = launch_prefill_prepare(sh, segs, ws, st, views);
   if (e != hipSuccess) return e;
-  return launch_prefill_run(sh, segs.n, views, q, M, sm_scale, o, lse, seg_lse, ws, st);
+  return launch_prefill_run(sh, segs, views, q, M, sm_scale, o, lse, seg_lse, ws, ws_bytes, st);
 }
 
 }  // namespace uc

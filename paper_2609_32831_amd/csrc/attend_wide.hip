@@ -117,13 +117,18 @@ struct State {
 // errors of one long chain were larger than those of a wave-wide sum.
 template <int D>
 __device__ inline f4 tile_scores(const float (&kf)[D / 4], const float (&qf)[D / 4]) {
-  constexpr int N = 8;
-  f4 a[N];
+  f4 s[D / 64];
 #pragma unroll
-  for (int i = 0; i < N; ++i) a[i] = f4{0.f, 0.f, 0.f, 0.f};
+  for (int h = 0; h < D / 64; ++h) {
+    f4 a[8];
 #pragma unroll
-  for (int t = 0; t < D / 4; ++t) a[t % N] = mfma4(kf[t], qf[t], a[t % N]);
-  return ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+    for (int i = 0; i < 8; ++i) {
+      a[i] = mfma4(kf[16 * h + i], qf[16 * h + i], f4{0.f, 0.f, 0.f, 0.f});
+      a[i] = mfma4(kf[16 * h + 8 + i], qf[16 * h + 8 + i], a[i]);
+    }
+    s[h] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  }
+  return D == 64 ? s[0] : s[0] + s[D / 64 - 1];
 }
 
 // Softmax of a tile whose first `live` rows count (lazy reference maximum, as
