@@ -237,11 +237,12 @@ size_t generic_ws(const uc_shape& sh, const KSegs& ks, int rows_min, int max_chu
 }
 
 // The binary32 matrix-core kernel takes 16 query rows of a KV head per
-// workgroup and at least 64 rows (a tile per wave).  Chunks are cut so that
-// about three workgroups per CU exist: fewer left the short calls waiting on
-// one memory latency per tile, more only adds records to merge.  The chunk
-// bound (at most wgs + n_segs, at most one per 64 rows) never shrinks as
-// rows are added.
+// workgroup and 64 to 256 rows: at least a tile per wave; at most 64 rows per
+// wave, so that its running sums keep the length of the vector-ALU kernel's
+// (with 128 the error against 64 bits grew from 3.3e-7 to 4.2e-7).  Between
+// the two, chunks are cut so that about three workgroups per CU exist: fewer
+// left the short calls waiting on one memory latency per tile, more only adds
+// records to merge.  The chunk bound never shrinks as rows are added.
 int wide_wgs(const uc_shape& sh, int M) {
   const int64_t blocks = ((int64_t)(sh.Hq / sh.Hkv) * M + 15) / 16 * sh.B * sh.Hkv;
   return (int)std::max<int64_t>(1, 3 * device_cus() / blocks);
@@ -250,17 +251,19 @@ bool wide_ok(const uc_shape& sh, int M) {  // the launch's grid limits
   return ((int64_t)(sh.Hq / sh.Hkv) * M + 15) / 16 <= 65535 && (int64_t)sh.B * sh.Hkv <= 65535;
 }
 size_t wide_bytes(const uc_shape& sh, const KSegs& ks, int M, bool want_o) {
-  size_t fine = 0;
-  for (int i = 0; i < ks.n; ++i) fine += (ks.s[i].n_rows + 63) / 64;
-  const size_t chunks = std::min<size_t>(fine, (size_t)wide_wgs(sh, M) + ks.n);
+  size_t finest = 0, coarsest = 0;
+  for (int i = 0; i < ks.n; ++i) {
+    finest += (ks.s[i].n_rows + 63) / 64;
+    coarsest += (ks.s[i].n_rows + 255) / 256;
+  }
+  const size_t chunks = std::min(finest, std::max<size_t>((size_t)wide_wgs(sh, M) + ks.n, coarsest));
   return align256((size_t)sh.B * sh.Hq * M * chunks * (want_o ? sh.D + 2 : 2) * sizeof(float));
 }
 ChunkPlan wide_plan(const uc_shape& sh, const KSegs& ks, int M) {
   int64_t total = 0;
   for (int i = 0; i < ks.n; ++i) total += ks.s[i].n_rows;
   const int64_t per = (total + wide_wgs(sh, M) - 1) / wide_wgs(sh, M);
-  return make_plan(ks, (int)std::min<int64_t>((std::max<int64_t>(per, 1) + 63) / 64 * 64, 1 << 30),
-                   1 << 30);
+  return make_plan(ks, (int)std::min<int64_t>((std::max<int64_t>(per, 1) + 63) / 64 * 64, 256), 1 << 30);
 }
 bool wide_path(const uc_shape& sh, int M) { return g_path.load() == UC_PATH_AUTO && wide_ok(sh, M); }
 

@@ -199,7 +199,7 @@ __global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int 
   l *= sc;
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
-  if (lse && lane == 0) lse[qi] = (M + log2f(l)) * kLn2;
+  if (lse && lane == 0) lse[qi] = (float)(((double)M + (double)log2f(l)) * kLn2d);
   if (o) {
     const float inv = 1.0f / l;
 #pragma unroll

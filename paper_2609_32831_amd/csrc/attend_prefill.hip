@@ -610,7 +610,7 @@ __global__ __launch_bounds__(256) void split_merge_kernel(int Q, int n, int nseg
     M = mx;
   }
   *reinterpret_cast<f2*>(o + qi * D + 2 * lane) = acc * (1.0f / l);
-  if (lse && lane == 0) lse[qi] = (M + log2f(l)) * kLn2;
+  if (lse && lane == 0) lse[qi] = (float)(((double)M + (double)log2f(l)) * kLn2d);
   if (seg_lse && lane < nseg) {
     const float* ps = sp.seg + qi * n * nseg + lane;
     float m = -INFINITY, t = 0.0f;

@@ -1,21 +1,21 @@
-// attend_wide.hip -- attention and importance scores in binary32 on the
+// attend_wide.hip -- attention and importance scores in binary32 or better on the
 // matrix cores, for every input outside the bf16 kernels: fp32 / fp16 rows or
 // queries, head dim 64, 8-bit codes, row groups below 32, any mixture of
 // element types (App. E, "Attention over heterogeneous cache segments" and
 // "Batched GQA token selection").
 //
-// Rows and queries are widened to binary32 (exact) and multiplied with
-// v_mfma_f32_16x16x4_f32, so every product and sum is a binary32 one.  A wave
-// takes 16-row tiles; nothing is staged in LDS, because the contraction may
+// Rows and queries are widened exactly; the logits are v_mfma_f64_16x16x4_f64
+// products rounded to binary32, the value products v_mfma_f32_16x16x4_f32.  A
+// wave takes 16-row tiles; nothing is staged in LDS, because the contraction may
 // run over the head dims and the keys in any order as long as both operands
 // agree on it:
 //   S^T = K Q^T   step t contracts dims g4*(D/4) + t (g4 = lane/16), so a lane
 //                 reads D/4 consecutive dims of key row lane%16;
-//   O^T += V^T P  step j contracts keys g4*4 + j, which is exactly where the
-//                 S^T result leaves them, so the probabilities are the B
+//   O^T += V^T P  step j contracts keys g4 + 4*j, which is exactly where the
+//                 binary64 S^T result leaves them, so the probabilities are the B
 //                 operand as they stand; output row i of dim tile t stands for
 //                 dim i*(D/16) + t, so a lane reads D/16 consecutive dims of
-//                 value row g4*4 + j.
+//                 value row g4 + 4*j.
 // Each loop holds the raw rows (or codes and value scales) of the next tile
 // in flight while it computes the current one.
 //
@@ -31,6 +31,7 @@ namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
+typedef double d4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
@@ -112,23 +113,22 @@ struct State {
   f4 acc[D / 16];
 };
 
-// The tile's logits: s[j] = <q, k> for key row g4*4 + j of the tile and query
-// column lane%16.  Short chains of products, added as a tree: the rounding
-// errors of one long chain were larger than those of a wave-wide sum.
+// The tile's logits: s[j] = <q, k> for key row g4 + 4*j of the tile and query
+// column lane%16, in binary64 and rounded once: in binary32 their rounding was
+// the largest error of a pass (3.3e-7 against 64 bits for a wave-wide sum on
+// the vector ALUs, 3.4e-7 to 3.8e-7 for short chains of binary32 matrix
+// products, 2.1e-7 so; 43 fp16 rows over 4085).  These products take twice the
+// time of binary32 ones (28 -> 32 us for the fp16 step above).
 template <int D>
 __device__ inline f4 tile_scores(const float (&kf)[D / 4], const float (&qf)[D / 4]) {
-  f4 s[D / 64];
+  d4 a = d4{0., 0., 0., 0.}, b = a;
 #pragma unroll
-  for (int h = 0; h < D / 64; ++h) {
-    f4 a[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      a[i] = mfma4(kf[16 * h + i], qf[16 * h + i], f4{0.f, 0.f, 0.f, 0.f});
-      a[i] = mfma4(kf[16 * h + 8 + i], qf[16 * h + 8 + i], a[i]);
-    }
-    s[h] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+  for (int t = 0; t < D / 4; t += 2) {
+    a = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[t], (double)qf[t], a, 0, 0, 0);
+    b = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[t + 1], (double)qf[t + 1], b, 0, 0, 0);
   }
-  return D == 64 ? s[0] : s[0] + s[D / 64 - 1];
+  a += b;
+  return f4{(float)a[0], (float)a[1], (float)a[2], (float)a[3]};
 }
 
 // Softmax of a tile whose first `live` rows count (lazy reference maximum, as
@@ -138,7 +138,7 @@ __device__ inline void tile_softmax(State<D>& st, const f4& s, float scale_log2,
                                     const float (&vf)[4][D / 16], int g4) {
   float p[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) p[j] = g4 * 4 + j < live ? s[j] : -INFINITY;
+  for (int j = 0; j < 4; ++j) p[j] = g4 + 4 * j < live ? s[j] : -INFINITY;
   // the scale is positive: the maximum of the raw logits gives the maximum
   float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])) * scale_log2;
   if (__builtin_amdgcn_ballot_w64(mx > st.m + kLazy)) {
@@ -157,10 +157,17 @@ __device__ inline void tile_softmax(State<D>& st, const f4& s, float scale_log2,
   for (int j = 0; j < 4; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(p[j], scale_log2, -st.m));
   st.l += (p[0] + p[1]) + (p[2] + p[3]);
   if (WANT_O) {
+    // the tile's product on its own, then one addition: sums of 16 rows and
+    // of a few tiles round less than one running sum
+    f4 pv[D / 16];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int t = 0; t < D / 16; ++t) pv[t] = mfma4(vf[0][t], p[0], f4{0.f, 0.f, 0.f, 0.f});
 #pragma unroll
-      for (int t = 0; t < D / 16; ++t) st.acc[t] = mfma4(vf[j][t], p[j], st.acc[t]);
+    for (int j = 1; j < 4; ++j)
+#pragma unroll
+      for (int t = 0; t < D / 16; ++t) pv[t] = mfma4(vf[j][t], p[j], pv[t]);
+#pragma unroll
+    for (int t = 0; t < D / 16; ++t) st.acc[t] += pv[t];
   }
 }
 
@@ -183,7 +190,7 @@ struct DenseSrc {
     if (WANT_O) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        r.v[j].load(v + min(row0 + g4 * 4 + j, n - 1) * RB + i16 * (RB / 16));
+        r.v[j].load(v + min(row0 + g4 + 4 * j, n - 1) * RB + i16 * (RB / 16));
     }
   }
   __device__ inline void keys(const Raw& r, int, int, int, float (&kf)[D / 4]) const {
@@ -228,7 +235,7 @@ struct PackedSrc {
     if (WANT_O) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int row = min(row0 + g4 * 4 + j, n - 1);
+        const int row = min(row0 + g4 + 4 * j, n - 1);
         uint32_t x[(VB + 3) / 4];
         bytes<VB>(cv + (int64_t)row * RB + i16 * VB, x);
         r.v[j][0] = x[0];
@@ -524,7 +531,7 @@ __global__ __launch_bounds__(256) void record_merge_kernel(int Q, int C,
   const float inv = 1.0f / l;
 #pragma unroll
   for (int i = 0; i < PER; ++i) o[(int64_t)qi * D + PER * lane + i] = acc[i] * inv;
-  if (lse && lane == 0) lse[qi] = (M + log2f(l)) * kLn2;
+  if (lse && lane == 0) lse[qi] = (float)(((double)M + (double)log2f(l)) * kLn2d);
 }
 
 // ---------------------------------------------------------------- scores
@@ -535,7 +542,7 @@ struct ScorePtrs {
 // Importance scores, second pass.  grid (chunks of 64 keys, b*h_kv): a wave
 // holds one 16-key tile and runs it against every query row of the head, 64
 // rows staged in LDS at a time.  S = Q K^T leaves a lane four query rows
-// (g4*4 + j) of its key (lane%16), so the sum over queries runs in the lane,
+// (g4 + 4*j) of its key (lane%16), so the sum over queries runs in the lane,
 // in double, and the four lanes of a key are added at the end.
 template <int D>
 __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPlan plan,
@@ -630,9 +637,8 @@ __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPla
         qf[i + 3] = x[3];
       }
       const f4 sv = tile_scores<D>(qf, kf);
-      const f4 lv = *reinterpret_cast<const f4*>(&ls[t * ROWS + g4 * 4]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc += (double)exp2f(fmaf(sv[j], scale_log2, -lv[j]));
+      for (int j = 0; j < 4; ++j) acc += (double)exp2f(fmaf(sv[j], scale_log2, -ls[t * ROWS + g4 + 4 * j]));
     }
   }
   acc += __shfl_xor(acc, 16, 64);

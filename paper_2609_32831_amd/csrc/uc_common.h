@@ -165,6 +165,7 @@ __device__ inline double wave_sum_d(double x) {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr double kLn2d = 0.6931471805599453;
 
 }  // namespace uc
 
