@@ -33,11 +33,12 @@ hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void*
                               const void* q, int M, float sm_scale, float* o, float* lse,
                               float* seg_lse, void* ws, size_t ws_bytes, hipStream_t st);
 int score_mfma_chunk_rows();
+int64_t score_mfma_col_slots(int64_t base);
 hipError_t launch_score_lse_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                                  const void* q, int W, float sm_scale, float* partial,
                                  hipStream_t st);
 hipError_t launch_score_col_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
-                                 const void* q, int W, int q_ld, float sm_scale, const float* lse,
+                                 const void* q, int W, int q_ld, float sm_scale, const float* norm,
                                  float* const* scores, double* mass_partial, double* colpart,
                                  hipStream_t st);
 int score_mfma_qblocks(int nq);
@@ -833,25 +834,25 @@ static ChunkPlan score_mfma_plan(const KSegs& ks) {
   return make_plan(ks, score_mfma_chunk_rows(), 1 << 30);
 }
 
-// workspace parts: pass-1 records, row log-sum-exps, chunk masses (fp64),
+// workspace parts: pass-1 records, row normalisers (reference, 1 / sum), chunk masses (fp64),
 // and (matrix-core path) the column pass's per-group column sums (fp64);
 // every part grows monotonically with the row counts
 static void score_ws_parts(const uc_shape& sh, const KSegs& ks, int W, bool fast, size_t& part1,
-                           size_t& lse_b, size_t& mass_b, size_t& col_b) {
-  lse_b = align256((size_t)sh.B * sh.Hq * W * sizeof(float));
+                           size_t& norm_b, size_t& mass_b, size_t& col_b) {
+  norm_b = align256((size_t)sh.B * sh.Hq * W * 2 * sizeof(float));
   col_b = 0;
   if (fast) {
     const ChunkPlan p = score_mfma_plan(ks);
     const int C = p.n_chunks;
     part1 = align256((size_t)sh.B * sh.Hq * W * C * 2 * sizeof(float));
     mass_b = align256((size_t)sh.B * sh.Hkv * C * sizeof(double));
-    // groups x chunks x heads is at most min(query blocks, 512 / (chunks x
-    // heads) + 1) x chunks x heads: sized by that bound, which (unlike the
-    // group count itself) never shrinks as rows are added
+    // sized by the bound of groups x chunks x heads, which (unlike the group
+    // count itself) never shrinks as rows are added
     const size_t base = (size_t)sh.B * sh.Hkv * C;
     const size_t qb = (size_t)score_mfma_qblocks((sh.Hq / sh.Hkv) * W);
     if (qb > 1)
-      col_b = align256(std::min(qb * base, 512 + base) * score_mfma_chunk_rows() * sizeof(double));
+      col_b = align256(std::min(qb * base, (size_t)score_mfma_col_slots(base)) * score_mfma_chunk_rows() *
+                       sizeof(double));
     return;
   }
   part1 = std::max(generic_ws(sh, ks, kLseRows, kLseMaxChunks, W, false),
@@ -892,7 +893,7 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
     return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t s = (hipStream_t)stream;
   float* partial = (float*)ws;
-  float* lse = (float*)((char*)ws + a);
+  float* norm = (float*)((char*)ws + a);
   double* mpart = (double*)((char*)ws + a + b);
   double* colpart = d ? (double*)((char*)ws + a + b + c) : nullptr;
   float* sp[kMaxSeg] = {};
@@ -904,9 +905,9 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
   if (fast) {
     const ChunkPlan p = score_mfma_plan(ks);
     e = launch_score_lse_mfma(*shape, ks, p, q_obs, W, sm_scale, partial, s);
-    if (e == hipSuccess) e = launch_attend_combine(*shape, ks, p, W, partial, nullptr, lse, nullptr, s);
+    if (e == hipSuccess) e = launch_score_norm((int64_t)shape->B * shape->Hq * W, p.n_chunks, partial, norm, s);
     if (e == hipSuccess)
-      e = launch_score_col_mfma(*shape, ks, p, q_obs, W, W, sm_scale, lse, sp, mpart, colpart, s);
+      e = launch_score_col_mfma(*shape, ks, p, q_obs, W, W, sm_scale, norm, sp, mpart, colpart, s);
     p2 = p;
   } else {
     const bool wide = wide_path(*shape, W);
@@ -914,10 +915,10 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
     p2 = score_col_plan(*shape, ks, W);
     e = wide ? launch_attend_wide(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s)
              : launch_attend_generic(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s);
-    if (e == hipSuccess) e = launch_attend_combine(*shape, ks, p1, W, partial, nullptr, lse, nullptr, s);
+    if (e == hipSuccess) e = launch_score_norm((int64_t)shape->B * shape->Hq * W, p1.n_chunks, partial, norm, s);
     if (e == hipSuccess)
-      e = wide ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, lse, sp, mpart, s)
-               : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, lse, sp, mpart, s);
+      e = wide ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, norm, sp, mpart, s)
+               : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, W, sm_scale, norm, sp, mpart, s);
   }
   if (e == hipSuccess && mass_out)
     e = launch_mass_finalize(p2, shape->B * shape->Hkv, n_segs, mpart, mass_out, s);
@@ -961,20 +962,20 @@ uc_status uc_score_columns(const uc_shape* shape, const uc_segment* segs, int n_
     for (int i = 0; i < n_segs; ++i)
       if (!sp[i]) kp.s[i].n_rows = 0;
   hipStream_t s = (hipStream_t)stream;
-  float* lse = (float*)((char*)ws + a);
+  float* norm = (float*)((char*)ws + a);
   double* mpart = mass_out ? (double*)((char*)ws + a + b) : nullptr;
   double* colpart = d ? (double*)((char*)ws + a + b + c) : nullptr;
   const ChunkPlan p2 = fast ? score_mfma_plan(kp) : score_col_plan(*shape, kp, W);
   hipError_t e = hipSuccess;
   if (p2.n_chunks > 0) {
-    e = launch_lse_rows(row_lse, lse_ld, W, shape->B * shape->Hq, lse, s);
+    e = launch_norm_rows(row_lse, lse_ld, W, shape->B * shape->Hq, norm, s);
     if (e == hipSuccess)
-      e = fast ? launch_score_col_mfma(*shape, ks, p2, q_obs, W, (int)q_ld, sm_scale, lse, sp,
+      e = fast ? launch_score_col_mfma(*shape, ks, p2, q_obs, W, (int)q_ld, sm_scale, norm, sp,
                                        mpart, colpart, s)
           : wide_path(*shape, W)
-               ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, lse, sp,
+               ? launch_score_wide(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, norm, sp,
                                    mpart, s)
-               : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, lse, sp,
+               : launch_score_colsum(*shape, ks, p2, q_obs, q_dt, W, (int)q_ld, sm_scale, norm, sp,
                                      mpart, s);
   }
   if (e == hipSuccess && mass_out)

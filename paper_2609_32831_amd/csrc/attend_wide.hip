@@ -549,12 +549,12 @@ __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPla
                                                             const void* __restrict__ q, int q_dt,
                                                             int Hq, int Hkv, int W, int q_ld,
                                                             float scale_log2,
-                                                            const float* __restrict__ lse,
+                                                            const f2* __restrict__ norm,
                                                             ScorePtrs scores,
                                                             double* __restrict__ mass_partial) {
   constexpr int QB = 64, QS = D + 4;  // query rows per round, floats per staged row
   __shared__ __attribute__((aligned(16))) float qs[QB * QS];
-  __shared__ __attribute__((aligned(16))) float ls[QB];
+  __shared__ __attribute__((aligned(16))) f2 ls[QB];
   __shared__ double red[WAVES];
   const int c = blockIdx.x, bh = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -624,7 +624,7 @@ __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPla
     }
     // rows past the window: p = exp2(-inf) = 0
     if (threadIdx.x < QB)
-      ls[threadIdx.x] = (int)threadIdx.x < n ? lse[(int64_t)bh * nq + q0 + threadIdx.x] * kLog2e : INFINITY;
+      ls[threadIdx.x] = (int)threadIdx.x < n ? norm[(int64_t)bh * nq + q0 + threadIdx.x] : f2{INFINITY, 0.0f};
     __syncthreads();
     for (int t = 0; t < tiles; ++t) {
       float qf[D / 4];
@@ -638,7 +638,10 @@ __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPla
       }
       const f4 sv = tile_scores<D>(qf, kf);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc += (double)exp2f(fmaf(sv[j], scale_log2, -ls[t * ROWS + g4 + 4 * j]));
+      for (int j = 0; j < 4; ++j) {
+        const f2 row = ls[t * ROWS + g4 + 4 * j];
+        acc = fma((double)exp2f(fmaf(sv[j], scale_log2, -row[0])), (double)row[1], acc);
+      }
     }
   }
   acc += __shfl_xor(acc, 16, 64);
@@ -688,14 +691,14 @@ int score_wide_chunk_rows() { return WAVES * ROWS; }
 
 hipError_t launch_score_wide(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                              const void* q, int q_dt, int W, int q_ld, float sm_scale,
-                             const float* lse, float* const* scores, double* mass_partial,
+                             const float* norm, float* const* scores, double* mass_partial,
                              hipStream_t st) {
   ScorePtrs sp{};
   for (int i = 0; i < segs.n; ++i) sp.p[i] = scores ? scores[i] : nullptr;
   const dim3 grid(plan.n_chunks, sh.B * sh.Hkv);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, st, segs, plan, q, q_dt, sh.Hq, sh.Hkv, W,
-                       q_ld, sm_scale * kLog2e, lse, sp, mass_partial);
+                       q_ld, sm_scale * kLog2e, (const f2*)norm, sp, mass_partial);
   };
   sh.D == 64 ? go(score_wide_kernel<64>) : go(score_wide_kernel<128>);
   return hipGetLastError();

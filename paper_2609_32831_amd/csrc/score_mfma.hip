@@ -16,14 +16,24 @@
 //           of the head; the per-key sums are written as the scores and
 //           their total is the chunk's probability mass (Eq. 1 bracket).
 // Both passes compute S^T = K Q^T with v_mfma_f32_16x16x32_bf16: a wave
-// takes 32-key tiles of the chunk (keys straight from HBM into the A-operand
-// layout; packed rows decoded in registers to their stored bf16 values) and
-// runs them against every 16-row query tile of the block, whose B operands
-// it reads from the block staged in LDS.  Logits are in base 2 (q.k times
+// takes pairs of 32-key tiles of the chunk (keys straight from HBM into the
+// A-operand layout; packed rows decoded in registers to their stored bf16
+// values) and runs each pair against every 16-row query tile of the block,
+// whose B operands it reads from the block staged in LDS.  The next pair is
+// loaded while the current one is computed.  Logits are in base 2 (q.k times
 // scale*log2(e)).
+// Row normalisers: a record is (m, l), l the sum of exp2(s - m), with m a
+// reference that is at most kLazy below the row's maximum; the records of a
+// row merge to (M, 1/l) and a probability is exp2(s - M) * (1/l), so no
+// log-sum-exp is rounded to binary32 on the way (its rounding, and that of
+// the change of base, was the largest error of the scores: 5.5e-7 to 1e-6
+// against 64 bits on 64k rows with heavy-tailed keys).
 // Column sums: a lane sums its key's probabilities over the query tiles in
-// fp32, the 16 query columns of a tile are added by a butterfly, and the
+// fp32, the 16 query columns of a tile are added across lanes, and the
 // query blocks are accumulated in fp64 in LDS; chunk masses are fp64.
+// Bound: the vector ALU.  Per 16 logits a lane spends 16 v_exp_f32 (two issue
+// slots each), 16 v_fma for the argument, 16 adds and, in pass 1, 8 v_max3 and
+// about 25 instructions of row bookkeeping, beside 16 matrix instructions.
 #include <algorithm>
 
 #include "mfma_util.h"
@@ -35,17 +45,17 @@ namespace {
 using namespace mf;
 
 constexpr int WAVES = 4;
-constexpr int TPW = 4;               // key tiles per wave and sub-chunk
-constexpr int SUB = WAVES * TPW * TILE;  // 512 keys per sub-chunk (K held in registers)
-constexpr int CHUNK = 2 * SUB;       // keys per workgroup
-constexpr int QB = 256;              // query rows per block (16 tiles)
+constexpr int TPW = 2;                   // key tiles per wave and step
+constexpr int SUB = WAVES * TPW * TILE;  // 256 keys per step (K held in registers, the next step's in flight)
+constexpr int CHUNK = 4 * SUB;           // keys per workgroup
+constexpr int QB = 256;                  // query rows per block (16 tiles)
 constexpr int QT = QB / 16;
-constexpr int QROW = D * 2 + 16;     // bytes of one staged query row (16 B padding)
-constexpr float kLazy = 8.0f;
+constexpr int QROW = D * 2 + 16;         // bytes of one staged query row (16 B padding)
+constexpr float kLazy = 8.0f;            // a row's reference may trail its maximum by this (base 2)
 
-// A wave's TPW key tiles of a sub-chunk as A operands: k[i][blk*4 + t] =
-// row (tile i) blk*16 + i16, dims t*32 + g4*8 .. +7.  Rows past the
-// descriptor's end read as zeros.
+// A wave's key tiles of a step as A operands: k[i][blk*4 + t] = row (tile i)
+// blk*16 + i16, dims t*32 + g4*8 .. +7.  Rows past the descriptor's end read
+// as zeros.
 struct KTiles {
   u4 k[TPW][8];
 };
@@ -163,6 +173,13 @@ __device__ inline void k_load(const KSrc& src, int row0, int lane, u4 (&k)[8]) {
   }
 }
 
+// the wave's key tiles of a step, from row0 on
+template <bool PACKED>
+__device__ inline void k_step(const KSrc& src, int row0, int lane, KTiles& K) {
+#pragma unroll
+  for (int i = 0; i < TPW; ++i) k_load<PACKED>(src, row0 + i * TILE, lane, K.k[i]);
+}
+
 // B operands (Q^T) of query tile qt, four 32-dim steps, from the staged block
 __device__ inline void q_tile(const char* qs, int qt, int lane, u4 (&qb)[4]) {
   const int i16 = lane & 15, g4 = lane >> 4;
@@ -207,121 +224,153 @@ __device__ inline int chunk_rows(const ChunkPlan& p, const KSegs& segs, int c, i
   return si;
 }
 
-// raw logits of one lane for one key tile: 8 keys (tile rows g4*4 + j and
-// 16 + g4*4 + j); with MASK, keys at or past r1 are -inf
-template <bool MASK>
-__device__ inline void logits(const f4& s0, const f4& s1, int row0, int r1, int g4, float* x) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    x[j] = !MASK || row0 + g4 * 4 + j < r1 ? s0[j] : -INFINITY;
-    x[4 + j] = !MASK || row0 + 16 + g4 * 4 + j < r1 ? s1[j] : -INFINITY;
-  }
+// sum over the four key-row lanes (g4) of a query column, in all four
+__device__ inline float sum_g4(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
-// Pass 1 on two key tiles (16 keys of the lane's query column): the lane's
-// running (m, l) over base-2 logits, re-referenced to the maximum so far, so
-// every v_exp_f32 argument is <= 0 (probabilities below 2^-126 of the
-// reference flush to zero).  A lane with no valid key yet keeps m = -inf and
-// l = 0.
+// The logits S^T of a wave's two key tiles against one query tile.
+typedef f4 Pair[TPW][2];
+
+__device__ inline void s_pair(const KTiles& K, const u4 (&qb)[4], Pair& s) {
+  s_tile(K.k[0], qb, s[0][0], s[0][1]);
+  s_tile(K.k[1], qb, s[1][0], s[1][1]);
+}
+
+// Pass 1 on one query tile: the row state (m, l) of query column i16 over the
+// 16 keys of each of its four lanes.  m is re-referenced only when some row of
+// the tile has a logit more than kLazy above it (every v_exp_f32 argument is
+// at most kLazy, up to 256 times 1024 terms), which is rare after a chunk's
+// first step: the merge of maxima across lanes and the rescaling took a sixth
+// of the loop when every tile did them.  A row with no valid key yet keeps
+// m = -inf and l = 0.
 template <bool MASK>
-__device__ inline void lse_half(const f4 (&s)[2][2], int row0a, int row0b, int r1, int g4,
-                                float scale_log2, float& m, float& l) {
+__device__ inline void lse_tile(const Pair& s, int row0, int r1, int g4, float scale_log2,
+                                float* rm, float* rl) {
   float x[16];
-  logits<MASK>(s[0][0], s[0][1], row0a, r1, g4, x);
-  logits<MASK>(s[1][0], s[1][1], row0b, r1, g4, x + 8);
-  float mx[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) mx[j] = fmaxf(fmaxf(x[j], x[4 + j]), fmaxf(x[8 + j], x[12 + j]));
-  // the scale is positive: the maximum of the raw logits gives it
-  const float mn = fmaxf(m, fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])) * scale_log2);
-  const float ref = mn == -INFINITY ? 0.0f : mn;
+  for (int i = 0; i < TPW; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        x[i * 8 + h * 4 + j] = !MASK || row0 + i * TILE + h * 16 + g4 * 4 + j < r1 ? s[i][h][j] : -INFINITY;
+  float m = *rm, l = *rl;
+  // maximum of the raw logits, NaN if there is one (the scale is positive);
+  // v_maximum3 takes them as they are, where fmaxf first quiets each operand
+  float mx = x[0];
+#pragma unroll
+  for (int j = 1; j < 15; j += 2)
+    mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, x[j]), x[j + 1]);
+  mx = __builtin_elementwise_maximum(mx, x[15]);
+  if (__any(!(mx * scale_log2 <= m + kLazy))) {
+    float top = -INFINITY;  // the largest that is not a NaN
+#pragma unroll
+    for (int j = 0; j < 16; ++j) top = fmaxf(top, x[j]);
+    top = fmaxf(top, __shfl_xor(top, 16, 64));
+    top = fmaxf(top, __shfl_xor(top, 32, 64));
+    const float mn = fmaxf(m, top * scale_log2);
+    l = m == -INFINITY ? l : l * __builtin_amdgcn_exp2f(m - mn);
+    m = mn;
+    *rm = m;
+  }
+  const float ref = m == -INFINITY ? 0.0f : m;
   float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int j = 0; j < 16; ++j) e[j & 3] += __builtin_amdgcn_exp2f(fmaf(x[j], scale_log2, -ref));
-  l = fmaf(l, __builtin_amdgcn_exp2f(m - ref), (e[0] + e[1]) + (e[2] + e[3]));
-  m = mn;
+  *rl = l + sum_g4((e[0] + e[1]) + (e[2] + e[3]));
 }
 
-// Pass 2 on two key tiles: p = exp2(s - lse) added to the lanes' column sums
-// (p <= 1 since s <= lse; probabilities below 2^-126 flush to zero)
-__device__ inline void col_half(const f4 (&s)[2][2], float lq, float scale_log2, float (&c0)[8],
-                                float (&c1)[8]) {
+// Pass 2 on one query tile: probabilities added to the lanes' column sums
+// (those below 2^-126 of the row's reference flush to zero)
+__device__ inline void col_tile(const Pair& s, f2 row, float scale_log2, float (&cs)[16]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    c0[j] += __builtin_amdgcn_exp2f(fmaf(s[0][0][j], scale_log2, -lq));
-    c0[4 + j] += __builtin_amdgcn_exp2f(fmaf(s[0][1][j], scale_log2, -lq));
-    c1[j] += __builtin_amdgcn_exp2f(fmaf(s[1][0][j], scale_log2, -lq));
-    c1[4 + j] += __builtin_amdgcn_exp2f(fmaf(s[1][1][j], scale_log2, -lq));
-  }
+  for (int i = 0; i < TPW; ++i)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float& c = cs[i * 8 + h * 4 + j];
+        c = fmaf(__builtin_amdgcn_exp2f(fmaf(s[i][h][j], scale_log2, -row[0])), row[1], c);
+      }
 }
 
-static_assert(TPW == 4, "the sub-chunk loops take a wave's key tiles in two pairs");
-
-// One sub-chunk of pass 1 for one wave.  The loop over query tiles keeps the
-// matrix cores and the vector ALUs busy together: while the exponentials of
-// one pair of key tiles run, the scores of the next pair are computed (the
-// pair (2, 3) of query tile t, then the pair (0, 1) of tile t + 1).  The
-// loop body has no branch, so the compiler can interleave the two.  rm / rl
-// hold the wave's (m, l) per query row; the four key-row lanes of a query
-// column agree after the merge and all store it.
+// One step of pass 1 for one wave.  The loop keeps the matrix cores and the
+// vector ALUs busy together: while the exponentials of one query tile run, the
+// logits of the next are computed, in two sets of registers taken in turn.  An
+// odd last tile is joined by the one after it (staged as zero rows, never
+// read).  rm / rl hold the wave's (m, l) per query row; the four lanes of a
+// query column agree and all store them.
 template <bool MASK>
-__device__ inline void lse_sub(const KTiles& K, const char* qs, float* rm, float* rl, int nqt,
-                               int sc, int r1, int wave, int lane, float scale_log2) {
+__device__ inline void lse_step(const KTiles& K, const char* qs, float* rm, float* rl, int nqt,
+                                int row0, int r1, int lane, float scale_log2) {
   const int i16 = lane & 15, g4 = lane >> 4;
-  int row[TPW];
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) row[i] = sc + (wave + i * WAVES) * TILE;
-  u4 qb[4];
-  f4 sa[2][2], sb[2][2];
-  q_tile(qs, 0, lane, qb);
-  s_tile(K.k[0], qb, sa[0][0], sa[0][1]);
-  s_tile(K.k[1], qb, sa[1][0], sa[1][1]);
-  for (int t = 0; t < nqt; ++t) {
-    // the wave's state so far enters through one of the four key-row lanes
-    float m = rm[t * 16 + i16], l = rl[t * 16 + i16];
-    m = g4 == 0 ? m : -INFINITY;
-    l = g4 == 0 ? l : 0.0f;
-    s_tile(K.k[2], qb, sb[0][0], sb[0][1]);
-    s_tile(K.k[3], qb, sb[1][0], sb[1][1]);
-    lse_half<MASK>(sa, row[0], row[1], r1, g4, scale_log2, m, l);
-    q_tile(qs, t + 1 < nqt ? t + 1 : t, lane, qb);  // the last round's pair is unused
-    s_tile(K.k[0], qb, sa[0][0], sa[0][1]);
-    s_tile(K.k[1], qb, sa[1][0], sa[1][1]);
-    lse_half<MASK>(sb, row[2], row[3], r1, g4, scale_log2, m, l);
-    // merge the four key-row lanes (g4) of each query column
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float m2 = __shfl_xor(m, o, 64), l2 = __shfl_xor(l, o, 64);
-      const float mn = fmaxf(m, m2);
-      const float ref = mn == -INFINITY ? 0.0f : mn;
-      l = fmaf(l, __builtin_amdgcn_exp2f(m - ref), l2 * __builtin_amdgcn_exp2f(m2 - ref));
-      m = mn;
-    }
-    rm[t * 16 + i16] = m;
-    rl[t * 16 + i16] = l;
+  const int last = QT - 1;
+  u4 qa[4], qb[4];
+  Pair sa, sb;
+  q_tile(qs, 0, lane, qa);
+  q_tile(qs, 1, lane, qb);
+  s_pair(K, qa, sa);
+  for (int t = 0; t < nqt; t += 2) {
+    q_tile(qs, min(t + 2, last), lane, qa);  // the last round's tiles are unused
+    s_pair(K, qb, sb);
+    lse_tile<MASK>(sa, row0, r1, g4, scale_log2, rm + t * 16 + i16, rl + t * 16 + i16);
+    q_tile(qs, min(t + 3, last), lane, qb);
+    s_pair(K, qa, sa);
+    lse_tile<MASK>(sb, row0, r1, g4, scale_log2, rm + t * 16 + 16 + i16, rl + t * 16 + 16 + i16);
   }
 }
 
-// One sub-chunk of pass 2 for one wave, pipelined like pass 1.  Tiles past
-// r1 read zero rows; their sums land in column slots nobody reads.
-__device__ inline void col_sub(const KTiles& K, const char* qs, const float* ls, int nqt,
-                               int lane, float scale_log2, float (&cs)[TPW][8]) {
+// One step of pass 2 for one wave, pipelined like pass 1.  Rows past r1 read
+// as zeros; their sums land in column slots nobody reads.
+__device__ inline void col_step(const KTiles& K, const char* qs, const f2* ls, int nqt, int lane,
+                                float scale_log2, float (&cs)[16]) {
   const int i16 = lane & 15;
-  u4 qb[4];
-  f4 sa[2][2], sb[2][2];
-  q_tile(qs, 0, lane, qb);
-  s_tile(K.k[0], qb, sa[0][0], sa[0][1]);
-  s_tile(K.k[1], qb, sa[1][0], sa[1][1]);
-  for (int t = 0; t < nqt; ++t) {
-    const float lq = ls[t * 16 + i16];
-    s_tile(K.k[2], qb, sb[0][0], sb[0][1]);
-    s_tile(K.k[3], qb, sb[1][0], sb[1][1]);
-    col_half(sa, lq, scale_log2, cs[0], cs[1]);
-    q_tile(qs, t + 1 < nqt ? t + 1 : t, lane, qb);  // the last round's pair is unused
-    s_tile(K.k[0], qb, sa[0][0], sa[0][1]);
-    s_tile(K.k[1], qb, sa[1][0], sa[1][1]);
-    col_half(sb, lq, scale_log2, cs[2], cs[3]);
+  const int last = QT - 1;
+  u4 qa[4], qb[4];
+  Pair sa, sb;
+  q_tile(qs, 0, lane, qa);
+  q_tile(qs, 1, lane, qb);
+  s_pair(K, qa, sa);
+  for (int t = 0; t < nqt; t += 2) {
+    const f2 ra = ls[t * 16 + i16], rb = ls[t * 16 + 16 + i16];
+    q_tile(qs, min(t + 2, last), lane, qa);  // the last round's tiles are unused
+    s_pair(K, qb, sb);
+    col_tile(sa, ra, scale_log2, cs);
+    q_tile(qs, min(t + 3, last), lane, qb);
+    s_pair(K, qa, sa);
+    col_tile(sb, rb, scale_log2, cs);
   }
+}
+
+template <int CTRL>
+__device__ inline float dpp(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
+// One halving of the sum over the 16 lanes of a row: a lane keeps the upper
+// (hi) or lower N/2 values and adds its partner's share of them.
+template <int CTRL, int N>
+__device__ inline void halve(float (&v)[16], bool hi) {
+#pragma unroll
+  for (int j = 0; j < N / 2; ++j) {
+    const float keep = hi ? v[j + N / 2] : v[j], give = hi ? v[j] : v[j + N / 2];
+    v[j] = keep + dpp<CTRL>(give);
+  }
+}
+
+// Sums over the 16 lanes of a row, value i16 of the 16 in lane i16: partners
+// are i16 ^ 15, ^ 7, ^ 3 and ^ 1 (row mirror, half mirror, quad permutations),
+// 15 adds instead of 64 and one result to store per lane instead of 16.
+__device__ inline float column_sum(float (&v)[16], int i16) {
+  halve<0x140, 16>(v, i16 & 8);
+  halve<0x141, 8>(v, i16 & 4);
+  halve<0x1B, 4>(v, i16 & 2);
+  halve<0xB1, 2>(v, i16 & 1);
+  return v[0];
 }
 
 // ---------------------------------------------------------------- pass 1
@@ -350,15 +399,17 @@ __global__ __launch_bounds__(256, 2) void score_lse_kernel(KSegs segs, ChunkPlan
   __syncthreads();
 
   const KSrc src = k_source(ks, bh, r1);
+  // the wave's tiles of a step: rows sc + wave*TPW*TILE on
+  const int w0 = wave * TPW * TILE;
+  KTiles K, next;
+  k_step<PACKED>(src, r0 + w0, lane, next);
   for (int sc = r0; sc < r1; sc += SUB) {
-    // the wave's tiles of this sub-chunk: rows sc + (wave + i*WAVES)*TILE
-    KTiles K;
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) k_load<PACKED>(src, sc + (wave + i * WAVES) * TILE, lane, K.k[i]);
-    if (sc + SUB <= r1)
-      lse_sub<false>(K, qs, red_m[wave], red_l[wave], nqt, sc, r1, wave, lane, scale_log2);
+    K = next;
+    if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
+    if (sc + w0 + TPW * TILE <= r1)
+      lse_step<false>(K, qs, red_m[wave], red_l[wave], nqt, sc + w0, r1, lane, scale_log2);
     else
-      lse_sub<true>(K, qs, red_m[wave], red_l[wave], nqt, sc, r1, wave, lane, scale_log2);
+      lse_step<true>(K, qs, red_m[wave], red_l[wave], nqt, sc + w0, r1, lane, scale_log2);
   }
   __syncthreads();
   const int C = plan.n_chunks;
@@ -391,12 +442,12 @@ __global__ __launch_bounds__(256, 2) void score_col_kernel(KSegs segs, ChunkPlan
                                                            const uint16_t* __restrict__ q, int Hq,
                                                            int Hkv, int W, int q_ld,
                                                            float scale_log2,
-                                                           const float* __restrict__ lse,
+                                                           const f2* __restrict__ norm,
                                                            ScoreOut out,
                                                            double* __restrict__ mass_partial,
                                                            int qbs, double* __restrict__ colpart) {
   __shared__ __attribute__((aligned(16))) char qs[QB * QROW];
-  __shared__ float ls[QB];
+  __shared__ f2 ls[QB];
   __shared__ double colsum[CHUNK];
   __shared__ double red[WAVES];
   // the first pass walks heads and chunks in grid order, so this one walks
@@ -410,49 +461,31 @@ __global__ __launch_bounds__(256, 2) void score_col_kernel(KSegs segs, ChunkPlan
   const int si = chunk_rows(plan, segs, c, r0, r1);
   const KSeg& ks = segs.s[si];
   const uint16_t* qh = q + ((int64_t)b * Hq + hkv * G) * q_ld * D;
-  const float* lh = lse + ((int64_t)b * Hq + hkv * G) * W;
+  const f2* lh = norm + ((int64_t)b * Hq + hkv * G) * W;
   for (int e = threadIdx.x; e < CHUNK; e += blockDim.x) colsum[e] = 0.0;
 
   const KSrc src = k_source(ks, bh, r1);
   const int q_end = min(nq, (sg + 1) * qbs * QB);
+  const int w0 = wave * TPW * TILE;
+  KTiles K, next;
   for (int q0 = sg * qbs * QB; q0 < q_end; q0 += QB) {
     const int nqt = min(QT, (nq - q0 + 15) / 16);
     __syncthreads();  // the previous block's readers are done
     stage_q(qs, qh, q0, nq, W, q_ld);
     for (int r = threadIdx.x; r < QB; r += blockDim.x)
-      ls[r] = q0 + r < nq ? lh[q0 + r] * kLog2e : INFINITY;  // padded rows: p = 0
+      ls[r] = q0 + r < nq ? lh[q0 + r] : f2{INFINITY, 0.0f};  // padded rows: p = 0
     __syncthreads();
+    k_step<PACKED>(src, r0 + w0, lane, next);
     for (int sc = r0; sc < r1; sc += SUB) {
-      KTiles K;
+      K = next;
+      if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
+      float cs[16];
 #pragma unroll
-      for (int i = 0; i < TPW; ++i) k_load<PACKED>(src, sc + (wave + i * WAVES) * TILE, lane, K.k[i]);
-      float cs[TPW][8];
-#pragma unroll
-      for (int i = 0; i < TPW; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) cs[i][j] = 0.0f;
-      col_sub(K, qs, ls, nqt, lane, scale_log2, cs);
-      // sum the 16 query columns (lanes i16), then add to the chunk's sums
-#pragma unroll
-      for (int i = 0; i < TPW; ++i) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float v = cs[i][j];
-          v += __shfl_xor(v, 1, 64);
-          v += __shfl_xor(v, 2, 64);
-          v += __shfl_xor(v, 4, 64);
-          v += __shfl_xor(v, 8, 64);
-          cs[i][j] = v;
-        }
-        if (i16 == 0) {
-          const int kt = sc - r0 + (wave + i * WAVES) * TILE;  // tile offset in the chunk
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            colsum[kt + g4 * 4 + j] += (double)cs[i][j];
-            colsum[kt + 16 + g4 * 4 + j] += (double)cs[i][4 + j];
-          }
-        }
-      }
+      for (int j = 0; j < 16; ++j) cs[j] = 0.0f;
+      col_step(K, qs, ls, nqt, lane, scale_log2, cs);
+      // value i16 of a lane's 16: tile i16/8, its upper or lower 16 keys, key g4*4 + i16%4
+      const float v = column_sum(cs, i16);
+      colsum[sc - r0 + w0 + (i16 >> 3) * TILE + (i16 >> 2 & 1) * 16 + g4 * 4 + (i16 & 3)] += (double)v;
     }
   }
   __syncthreads();
@@ -533,13 +566,30 @@ static bool has_packed(const KSegs& segs, const ChunkPlan& plan) {
 
 int score_mfma_qblocks(int nq) { return (nq + QB - 1) / QB; }
 
-// query-block groups of the column pass: enough workgroups to fill the chip
-// (about 512) when chunks x heads alone do not
+// chunk sums that the groups of the column pass may leave to be added, for
+// `base` chunk-heads (grows with base)
+int64_t score_mfma_col_slots(int64_t base) { return 1024 + base; }
+
+// Query-block groups of the column pass.  A workgroup takes ceil(query blocks /
+// groups) of them and the chip holds two workgroups per CU, so the pass lasts
+// as many times that as rounds of workgroups are needed: the count with the
+// least of it, and of those the smallest (fewer partial sums to add).  72
+// chunk-heads of 112 blocks ran as 8 groups, 576 workgroups and two rounds of
+// 14 blocks; as 7 they are one round of 16.
 static int score_col_groups(const uc_shape& sh, const ChunkPlan& plan, int W) {
   const int qblocks = score_mfma_qblocks((sh.Hq / sh.Hkv) * W);
-  const int base = plan.n_chunks * sh.B * sh.Hkv;
-  const int want = (512 + base - 1) / base;
-  return std::max(1, std::min(qblocks, want));
+  const int64_t base = (int64_t)plan.n_chunks * sh.B * sh.Hkv, slots = 2 * device_cus();
+  const int64_t most = std::min<int64_t>(qblocks, score_mfma_col_slots(base) / base);
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int g = 1; g <= most; ++g) {
+    const int64_t cost = (base * g + slots - 1) / slots * ((qblocks + g - 1) / g);
+    if (cost < least) {
+      least = cost;
+      best = g;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_score_lse_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
@@ -557,7 +607,7 @@ hipError_t launch_score_lse_mfma(const uc_shape& sh, const KSegs& segs, const Ch
 }
 
 hipError_t launch_score_col_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
-                                 const void* q, int W, int q_ld, float sm_scale, const float* lse,
+                                 const void* q, int W, int q_ld, float sm_scale, const float* norm,
                                  float* const* scores, double* mass_partial, double* colpart,
                                  hipStream_t st) {
   ScoreOut so{};
@@ -569,11 +619,11 @@ hipError_t launch_score_col_mfma(const uc_shape& sh, const KSegs& segs, const Ch
   dim3 grid(plan.n_chunks, n_groups, sh.B * sh.Hkv);
   if (has_packed(segs, plan))
     hipLaunchKernelGGL(score_col_kernel<true>, grid, dim3(256), 0, st, segs, plan,
-                       (const uint16_t*)q, sh.Hq, sh.Hkv, W, q_ld, sm_scale * kLog2e, lse, so,
+                       (const uint16_t*)q, sh.Hq, sh.Hkv, W, q_ld, sm_scale * kLog2e, (const f2*)norm, so,
                        mass_partial, qbs, n_groups > 1 ? colpart : nullptr);
   else
     hipLaunchKernelGGL(score_col_kernel<false>, grid, dim3(256), 0, st, segs, plan,
-                       (const uint16_t*)q, sh.Hq, sh.Hkv, W, q_ld, sm_scale * kLog2e, lse, so,
+                       (const uint16_t*)q, sh.Hq, sh.Hkv, W, q_ld, sm_scale * kLog2e, (const f2*)norm, so,
                        mass_partial, qbs, n_groups > 1 ? colpart : nullptr);
   if (n_groups > 1)
     hipLaunchKernelGGL(score_col_reduce_kernel, dim3(plan.n_chunks, sh.B * sh.Hkv), dim3(256), 0,

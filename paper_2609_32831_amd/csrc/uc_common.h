@@ -203,11 +203,11 @@ hipError_t launch_record_merge(int D, int Q, int C, const float* partial, float*
 int score_wide_chunk_rows();
 hipError_t launch_score_wide(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                              const void* q, int q_dt, int W, int q_ld, float sm_scale,
-                             const float* lse, float* const* scores, double* mass_partial,
+                             const float* norm, float* const* scores, double* mass_partial,
                              hipStream_t st);
 hipError_t launch_score_colsum(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
                                const void* q, int q_dt, int W, int q_ld, float sm_scale,
-                               const float* lse,
+                               const float* norm,
                                float* const* scores, double* mass_partial, hipStream_t st);
 hipError_t launch_mass_finalize(const ChunkPlan& plan, int BH, int n_segs,
                                 const double* mass_partial, float* mass, hipStream_t st);
@@ -226,8 +226,12 @@ hipError_t launch_evict_step(int BH, int N, const float* scores, const int32_t* 
                              const void* ksrc, const void* vsrc, int64_t src_ld,
                              const int32_t* idx_src, void* kdst, void* vdst, int32_t* idx_dst,
                              int64_t dst_ld, int row_bytes, hipStream_t st);
-hipError_t launch_lse_rows(const float* src, int64_t ld, int W, int rows, float* dst,
-                          hipStream_t st);
+// Row normalisers of the scoring passes: two floats (m, r) per query row, the
+// row's probabilities being exp2(s - m) * r.  From pass-1 records, or from a
+// caller's natural log-sum-exps with a leading dimension.
+hipError_t launch_score_norm(int64_t Q, int C, const float* partial, float* norm, hipStream_t st);
+hipError_t launch_norm_rows(const float* src, int64_t ld, int W, int rows, float* norm,
+                            hipStream_t st);
 hipError_t launch_segment_mass(const uc_shape& sh, int M, int n_segs, const float* lse,
                                const float* seg_lse, float* mass, hipStream_t st);
 }  // namespace uc
