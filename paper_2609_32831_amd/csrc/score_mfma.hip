@@ -188,30 +188,35 @@ __device__ inline void q_tile(const char* qs, int qt, int lane, u4 (&qb)[4]) {
   for (int t = 0; t < 4; ++t) qb[t] = *reinterpret_cast<const u4*>(qrow + t * 64);
 }
 
-// S^T of a key tile against one query tile: s0 = keys 0..15, s1 = keys
-// 16..31; lane (i16, g4) holds keys g4*4 + j (+16) of query column i16
-__device__ inline void s_tile(const u4 (&k)[8], const u4 (&qb)[4], f4& s0, f4& s1) {
-  s0 = f4{0.f, 0.f, 0.f, 0.f};
-  s1 = s0;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    s0 = mfma(k[t], qb[t], s0);
-    s1 = mfma(k[4 + t], qb[t], s1);
-  }
-}
-
 // stage query rows [q0, q0 + QB) of the head's observation block (rows past nq
 // are zero) into LDS; row g*W + w of the block is window row w of the
 // group's query head g, which starts ld rows after head g - 1
 __device__ inline void stage_q(char* qs, const uint16_t* qh, int q0, int nq, int W, int ld) {
-  for (int e = threadIdx.x; e < QB * (D / 8); e += blockDim.x) {
-    const int r = e / (D / 8), c = e % (D / 8);
-    u4 v = u4{0, 0, 0, 0};
-    if (q0 + r < nq) {
-      const int g = (q0 + r) / W, w = q0 + r - g * W;
-      v = *reinterpret_cast<const u4*>(qh + ((int64_t)g * ld + w) * D + c * 8);
+  // half of a thread's chunks in flight at once: one memory latency per half,
+  // where a load and its store in turn took sixteen
+  constexpr int kThreads = 64 * WAVES, kEach = QB * (D / 8) / kThreads, kBatch = kEach / 2;
+  static_assert(kThreads % (D / 8) == 0 && kBatch * 2 * kThreads == QB * (D / 8), "whole batches");
+  const int c = threadIdx.x % (D / 8);
+#pragma unroll
+  for (int e0 = 0; e0 < kEach; e0 += kBatch) {
+    u4 v[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int r = ((int)threadIdx.x + (e0 + j) * kThreads) / (D / 8);
+      const int at = min(q0 + r, nq - 1);  // rows past the end: a valid row, zeroed below
+      int64_t row = at;
+      if (ld != W) {
+        const int g = at / W;
+        row = (int64_t)g * ld + (at - g * W);
+      }
+      v[j] = *reinterpret_cast<const u4*>(qh + row * D + c * 8);
     }
-    *reinterpret_cast<u4*>(qs + r * QROW + c * 16) = v;
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int r = ((int)threadIdx.x + (e0 + j) * kThreads) / (D / 8);
+      if (q0 + r >= nq) v[j] = u4{0, 0, 0, 0};
+      *reinterpret_cast<u4*>(qs + r * QROW + c * 16) = v[j];
+    }
   }
 }
 
@@ -232,44 +237,75 @@ __device__ inline float sum_g4(float x) {
   return __uint_as_float(t[0]) + __uint_as_float(t[1]);
 }
 
-// The logits S^T of a wave's two key tiles against one query tile.
+// The logits S^T of a wave's two key tiles against one query tile: s[i][h] =
+// keys h*16 .. h*16 + 15 of tile i, of which lane (i16, g4) holds keys
+// g4*4 + j of query column i16.
 typedef f4 Pair[TPW][2];
+static_assert(TPW == 2 && TILE == 32, "the tile loops are written out for 64 keys");
 
-__device__ inline void s_pair(const KTiles& K, const u4 (&qb)[4], Pair& s) {
-  s_tile(K.k[0], qb, s[0][0], s[0][1]);
-  s_tile(K.k[1], qb, s[1][0], s[1][1]);
+__device__ inline float pick(const Pair& s, int n) { return s[n >> 3][n >> 2 & 1][n & 3]; }
+
+// One half of the loops below: the logits of one query tile on the matrix
+// cores, and between them, one step of each kind per slot, the exponentials of
+// the tile before: slot n forms argument n, takes exponential n - 1 and adds
+// probability n - 2, so nothing waits for the instruction before it.  The
+// order is fixed by the scheduling barriers: left alone, the compiler puts the
+// matrix instructions together and the LDS reads next to their use, and the
+// two units took turns (680 cycles per 16 logits and SIMD, against 430 measured
+// for the same instructions side by side).
+template <class Arg, class Add>
+__device__ inline void s_pair(const KTiles& K, const u4 (&qb)[4], Pair& s, Arg arg, Add add) {
+  float x[16];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int n = 0; n < 18; ++n) {
+    if (n < 16) {
+      const int t = n >> 2, i = n >> 1 & 1, h = n & 1;
+      s[i][h] = mfma(K.k[i][h * 4 + t], qb[t], t == 0 ? f4{0.f, 0.f, 0.f, 0.f} : s[i][h]);
+      x[n] = arg(n);
+    }
+    if (n >= 1 && n <= 16) x[n - 1] = __builtin_amdgcn_exp2f(x[n - 1]);
+    if (n >= 2) add(n - 2, x[n - 2]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
-// Pass 1 on one query tile: the row state (m, l) of query column i16 over the
-// 16 keys of each of its four lanes.  m is re-referenced only when some row of
-// the tile has a logit more than kLazy above it (every v_exp_f32 argument is
-// at most kLazy, up to 256 times 1024 terms), which is rare after a chunk's
-// first step: the merge of maxima across lanes and the rescaling took a sixth
-// of the loop when every tile did them.  A row with no valid key yet keeps
-// m = -inf and l = 0.
+// the logits alone
+__device__ inline void s_pair(const KTiles& K, const u4 (&qb)[4], Pair& s) {
+#pragma unroll
+  for (int n = 0; n < 16; ++n) {
+    const int t = n >> 2, i = n >> 1 & 1, h = n & 1;
+    s[i][h] = mfma(K.k[i][h * 4 + t], qb[t], t == 0 ? f4{0.f, 0.f, 0.f, 0.f} : s[i][h]);
+  }
+}
+
+// Pass 1, one half: the row state (m, l) of query column i16 takes the 16 keys
+// of each of its four lanes in s, while the logits of query tile q go to
+// `next`.  m is re-referenced only when some row of the tile has a logit more
+// than kLazy above it (every v_exp_f32 argument is at most kLazy, up to 256
+// times 1024 terms), which is rare after a chunk's first step: the merge of
+// maxima across lanes and the rescaling took a sixth of the loop when every
+// tile did them.  A row with no valid key yet keeps m = -inf and l = 0.
 template <bool MASK>
-__device__ inline void lse_tile(const Pair& s, int row0, int r1, int g4, float scale_log2,
-                                float* rm, float* rl) {
-  float x[16];
+__device__ inline void lse_half(const KTiles& K, const u4 (&q)[4], Pair& next, Pair& s, int row0,
+                                int r1, int g4, float scale_log2, float* rm, float m, float* rl,
+                                float l) {
+  if (MASK) {
 #pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        x[i * 8 + h * 4 + j] = !MASK || row0 + i * TILE + h * 16 + g4 * 4 + j < r1 ? s[i][h][j] : -INFINITY;
-  float m = *rm, l = *rl;
+    for (int n = 0; n < 16; ++n)
+      if (row0 + (n >> 2) * 16 + g4 * 4 + (n & 3) >= r1) s[n >> 3][n >> 2 & 1][n & 3] = -INFINITY;
+  }
   // maximum of the raw logits, NaN if there is one (the scale is positive);
   // v_maximum3 takes them as they are, where fmaxf first quiets each operand
-  float mx = x[0];
+  float mx = pick(s, 0);
 #pragma unroll
-  for (int j = 1; j < 15; j += 2)
-    mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, x[j]), x[j + 1]);
-  mx = __builtin_elementwise_maximum(mx, x[15]);
+  for (int n = 1; n < 15; n += 2)
+    mx = __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, pick(s, n)), pick(s, n + 1));
+  mx = __builtin_elementwise_maximum(mx, pick(s, 15));
   if (__any(!(mx * scale_log2 <= m + kLazy))) {
     float top = -INFINITY;  // the largest that is not a NaN
 #pragma unroll
-    for (int j = 0; j < 16; ++j) top = fmaxf(top, x[j]);
+    for (int n = 0; n < 16; ++n) top = fmaxf(top, pick(s, n));
     top = fmaxf(top, __shfl_xor(top, 16, 64));
     top = fmaxf(top, __shfl_xor(top, 32, 64));
     const float mn = fmaxf(m, top * scale_log2);
@@ -278,32 +314,19 @@ __device__ inline void lse_tile(const Pair& s, int row0, int r1, int g4, float s
     *rm = m;
   }
   const float ref = m == -INFINITY ? 0.0f : m;
-  float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-  for (int j = 0; j < 16; ++j) e[j & 3] += __builtin_amdgcn_exp2f(fmaf(x[j], scale_log2, -ref));
+  float e[4];
+  s_pair(K, q, next, [&](int n) { return fmaf(pick(s, n), scale_log2, -ref); },
+         [&](int n, float p) { e[n & 3] = n < 4 ? p : e[n & 3] + p; });
   *rl = l + sum_g4((e[0] + e[1]) + (e[2] + e[3]));
-}
-
-// Pass 2 on one query tile: probabilities added to the lanes' column sums
-// (those below 2^-126 of the row's reference flush to zero)
-__device__ inline void col_tile(const Pair& s, f2 row, float scale_log2, float (&cs)[16]) {
-#pragma unroll
-  for (int i = 0; i < TPW; ++i)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        float& c = cs[i * 8 + h * 4 + j];
-        c = fmaf(__builtin_amdgcn_exp2f(fmaf(s[i][h][j], scale_log2, -row[0])), row[1], c);
-      }
 }
 
 // One step of pass 1 for one wave.  The loop keeps the matrix cores and the
 // vector ALUs busy together: while the exponentials of one query tile run, the
-// logits of the next are computed, in two sets of registers taken in turn.  An
-// odd last tile is joined by the one after it (staged as zero rows, never
-// read).  rm / rl hold the wave's (m, l) per query row; the four lanes of a
-// query column agree and all store them.
+// logits of the next are computed, in two sets of registers taken in turn, and
+// the operands and row states of the tile after are read from LDS.  An odd last
+// tile is joined by the one after it (staged as zero rows, never read).  rm /
+// rl hold the wave's (m, l) per query row; the four lanes of a query column
+// agree and all store them.
 template <bool MASK>
 __device__ inline void lse_step(const KTiles& K, const char* qs, float* rm, float* rl, int nqt,
                                 int row0, int r1, int lane, float scale_log2) {
@@ -313,19 +336,30 @@ __device__ inline void lse_step(const KTiles& K, const char* qs, float* rm, floa
   Pair sa, sb;
   q_tile(qs, 0, lane, qa);
   q_tile(qs, 1, lane, qb);
+  rm += i16;
+  rl += i16;
+  float ma = rm[0], la = rl[0], mb = rm[16], lb = rl[16];
   s_pair(K, qa, sa);
   for (int t = 0; t < nqt; t += 2) {
-    q_tile(qs, min(t + 2, last), lane, qa);  // the last round's tiles are unused
-    s_pair(K, qb, sb);
-    lse_tile<MASK>(sa, row0, r1, g4, scale_log2, rm + t * 16 + i16, rl + t * 16 + i16);
-    q_tile(qs, min(t + 3, last), lane, qb);
-    s_pair(K, qa, sa);
-    lse_tile<MASK>(sb, row0, r1, g4, scale_log2, rm + t * 16 + 16 + i16, rl + t * 16 + 16 + i16);
+    const int t2 = min(t + 2, last), t3 = min(t + 3, last);  // the last round's tiles are unused
+    q_tile(qs, t2, lane, qa);
+    float m = ma, l = la;
+    ma = rm[t2 * 16];
+    la = rl[t2 * 16];
+    lse_half<MASK>(K, qb, sb, sa, row0, r1, g4, scale_log2, rm + t * 16, m, rl + t * 16, l);
+    q_tile(qs, t3, lane, qb);
+    m = mb;
+    l = lb;
+    mb = rm[t3 * 16];
+    lb = rl[t3 * 16];
+    lse_half<MASK>(K, qa, sa, sb, row0, r1, g4, scale_log2, rm + t * 16 + 16, m, rl + t * 16 + 16, l);
   }
 }
 
-// One step of pass 2 for one wave, pipelined like pass 1.  Rows past r1 read
-// as zeros; their sums land in column slots nobody reads.
+// One step of pass 2 for one wave, pipelined like pass 1: probabilities added
+// to the lanes' column sums (those below 2^-126 of the row's reference flush to
+// zero).  Rows past r1 read as zeros; their sums land in column slots nobody
+// reads.
 __device__ inline void col_step(const KTiles& K, const char* qs, const f2* ls, int nqt, int lane,
                                 float scale_log2, float (&cs)[16]) {
   const int i16 = lane & 15;
@@ -334,15 +368,21 @@ __device__ inline void col_step(const KTiles& K, const char* qs, const f2* ls, i
   Pair sa, sb;
   q_tile(qs, 0, lane, qa);
   q_tile(qs, 1, lane, qb);
+  ls += i16;
+  f2 ra = ls[0], rb = ls[16];
   s_pair(K, qa, sa);
   for (int t = 0; t < nqt; t += 2) {
-    const f2 ra = ls[t * 16 + i16], rb = ls[t * 16 + 16 + i16];
-    q_tile(qs, min(t + 2, last), lane, qa);  // the last round's tiles are unused
-    s_pair(K, qb, sb);
-    col_tile(sa, ra, scale_log2, cs);
-    q_tile(qs, min(t + 3, last), lane, qb);
-    s_pair(K, qa, sa);
-    col_tile(sb, rb, scale_log2, cs);
+    const int t2 = min(t + 2, last), t3 = min(t + 3, last);  // the last round's tiles are unused
+    q_tile(qs, t2, lane, qa);
+    f2 r = ra;
+    ra = ls[t2 * 16];
+    s_pair(K, qb, sb, [&](int n) { return fmaf(pick(sa, n), scale_log2, -r[0]); },
+           [&](int n, float p) { cs[n] = fmaf(p, r[1], cs[n]); });
+    q_tile(qs, t3, lane, qb);
+    r = rb;
+    rb = ls[t3 * 16];
+    s_pair(K, qa, sa, [&](int n) { return fmaf(pick(sb, n), scale_log2, -r[0]); },
+           [&](int n, float p) { cs[n] = fmaf(p, r[1], cs[n]); });
   }
 }
 
@@ -391,18 +431,19 @@ __global__ __launch_bounds__(256, 2) void score_lse_kernel(KSegs segs, ChunkPlan
   const uint16_t* qh = q + ((int64_t)b * Hq + hkv * G) * W * D;
   const int q0 = qb * QB;
   const int nqt = min(QT, (nq - q0 + 15) / 16);
+  // the first keys are on their way while the queries are staged
+  const KSrc src = k_source(ks, bh, r1);
+  const int w0 = wave * TPW * TILE;
+  KTiles K, next;
+  k_step<PACKED>(src, r0 + w0, lane, next);
   stage_q(qs, qh, q0, nq, W, W);
-  for (int e = threadIdx.x; e < WAVES * QB; e += blockDim.x) {
+  for (int e = threadIdx.x; e < WAVES * QB; e += 64 * WAVES) {
     red_m[e / QB][e % QB] = -INFINITY;
     red_l[e / QB][e % QB] = 0.0f;
   }
   __syncthreads();
 
-  const KSrc src = k_source(ks, bh, r1);
   // the wave's tiles of a step: rows sc + wave*TPW*TILE on
-  const int w0 = wave * TPW * TILE;
-  KTiles K, next;
-  k_step<PACKED>(src, r0 + w0, lane, next);
   for (int sc = r0; sc < r1; sc += SUB) {
     K = next;
     if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
@@ -470,12 +511,12 @@ __global__ __launch_bounds__(256, 2) void score_col_kernel(KSegs segs, ChunkPlan
   KTiles K, next;
   for (int q0 = sg * qbs * QB; q0 < q_end; q0 += QB) {
     const int nqt = min(QT, (nq - q0 + 15) / 16);
+    k_step<PACKED>(src, r0 + w0, lane, next);
     __syncthreads();  // the previous block's readers are done
     stage_q(qs, qh, q0, nq, W, q_ld);
     for (int r = threadIdx.x; r < QB; r += blockDim.x)
       ls[r] = q0 + r < nq ? lh[q0 + r] : f2{INFINITY, 0.0f};  // padded rows: p = 0
     __syncthreads();
-    k_step<PACKED>(src, r0 + w0, lane, next);
     for (int sc = r0; sc < r1; sc += SUB) {
       K = next;
       if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
