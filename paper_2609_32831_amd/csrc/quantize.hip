@@ -113,92 +113,199 @@ __global__ void quantize_v_kernel(KSeg seg, const void* __restrict__ v, int dt, 
   }
 }
 
-// ---- vectorised forms for 2-byte dtypes and head dims 64 / 128: a lane
-// holds 8 consecutive channels of a row (one 16-byte load) and writes their
-// 8 codes as one 16-, 32- or 64-bit store.  Min and max are exact and the
-// scale, division and rounding are those of quant_code, so the results are
-// the same bits as the per-element forms above.
+// ---- vectorised forms for head dims 64 / 128: a lane holds 8 consecutive
+// channels of a row (one or two 16-byte loads) and writes their 8 codes as one
+// 16-, 32- or 64-bit store.  Min and max are exact and the scale and the codes
+// are those of quant_code, so the results are the same bits as the per-element
+// forms above.
 
-// 8 channels starting at element e (16-byte aligned) as floats
-__device__ inline void load8(const void* p, int dt, int64_t e, float (&x)[8]) {
-  const uint4 w = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(p) + e);
-  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+// Eight elements of a row as loaded (16-byte aligned).
+template <int DT>
+struct Raw8 {
+  uint4 w[DT == UC_F32 ? 2 : 1];
+  __device__ inline void load(const void* p, int64_t e) {
+    const uint4* q = reinterpret_cast<const uint4*>(static_cast<const char*>(p) + e * (DT == UC_F32 ? 4 : 2));
+    w[0] = q[0];
+    if constexpr (DT == UC_F32) w[1] = q[1];
+  }
+  __device__ inline void widen(float (&x)[8]) const {
+    if constexpr (DT == UC_F32) {
+      const uint32_t u[8] = {w[0].x, w[0].y, w[0].z, w[0].w, w[1].x, w[1].y, w[1].z, w[1].w};
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint16_t lo = (uint16_t)(u[j] & 0xFFFFu), hi = (uint16_t)(u[j] >> 16);
-    x[2 * j] = dt == UC_BF16 ? bf16_to_f32(lo) : f16_to_f32(lo);
-    x[2 * j + 1] = dt == UC_BF16 ? bf16_to_f32(hi) : f16_to_f32(hi);
+      for (int j = 0; j < 8; ++j) x[j] = __uint_as_float(u[j]);
+    } else {
+      const uint32_t u[4] = {w[0].x, w[0].y, w[0].z, w[0].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint16_t lo = (uint16_t)(u[j] & 0xFFFFu), hi = (uint16_t)(u[j] >> 16);
+        x[2 * j] = DT == UC_BF16 ? bf16_to_f32(lo) : f16_to_f32(lo);
+        x[2 * j + 1] = DT == UC_BF16 ? bf16_to_f32(hi) : f16_to_f32(hi);
+      }
+    }
+  }
+};
+
+// Scale of a group from its range, and the scale's reciprocal, without the
+// general division: correctly rounded like it where this returns true, which
+// is for ranges clear of underflow and overflow and for 0 (one value in the
+// group: scale, reciprocal and every code are 0).  Quotient and reciprocal come
+// from fused multiply-add corrections (Markstein 1990).  Checked over all
+// mantissas: range / (2^b - 1) is right after one correction; the reciprocal,
+// from any start within 2 units in the last place (v_rcp_f32 has 1), is right
+// after two steps except for a mantissa of all ones, which is left to the
+// caller.  Nine issue slots, where two general divisions took about thirty.
+__device__ inline bool plain_scale(float range, int b, float& s, float& r) {
+  const float qmax = (float)((1 << b) - 1);
+  const float c = b == 2 ? 1.0f / 3.0f : b == 4 ? 1.0f / 15.0f : 1.0f / 255.0f;
+  s = range * c;
+  s = __builtin_fmaf(__builtin_fmaf(-s, qmax, range), c, s);
+  r = __builtin_amdgcn_rcpf(s);
+  r = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+  r = __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+  if (!(s > 0.0f)) r = 0.0f;
+  return range == 0.0f || (range >= 0x1p-70f && range <= 0x1p80f &&
+                           (__float_as_uint(s) & 0x7FFFFFu) != 0x7FFFFFu);
+}
+
+// rint of the correctly rounded quotient d / s, from r = 1 / s correctly rounded:
+// two residual corrections by fused multiply-add, of which the first leaves a
+// faithful and the second the correctly rounded quotient (Markstein 1990).  s
+// and r are plain_scale's (r = 0 for s = 0).  Five instructions where the general
+// division takes about twelve, several of them at a quarter of the rate.
+__device__ inline uint32_t quotient_code(float d, float s, float r, float qmax) {
+  float q = d * r;
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, d), r, q);
+  q = __builtin_fmaf(__builtin_fmaf(-q, s, d), r, q);
+  return (uint32_t)__builtin_amdgcn_fmed3f(rintf(q), 0.0f, qmax);
+}
+
+// the B-bit codes of 8 consecutive channels (channel e at bit B*e) stored at p
+template <int B>
+__device__ inline void put_codes8(uint8_t* p, const uint32_t (&code)[8]) {
+  if constexpr (B == 8) {
+    uint2 w{0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      w.x |= code[e] << (8 * e);
+      w.y |= code[4 + e] << (8 * e);
+    }
+    *reinterpret_cast<uint2*>(p) = w;
+  } else {
+    uint32_t w = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w |= code[e] << (B * e);
+    if constexpr (B == 4) *reinterpret_cast<uint32_t*>(p) = w;
+    else *reinterpret_cast<uint16_t*>(p) = (uint16_t)w;
   }
 }
 
-// the b-bit codes of 8 consecutive channels (channel e at bit b*e) stored at p
-__device__ inline void store_codes8(uint8_t* p, const int (&code)[8], int b) {
-  uint64_t w = 0;
+template <int B>
+__device__ inline void codes8(uint8_t* p, const float (&x)[8], const float (&mn)[8],
+                              const float (&s)[8], const float (&r)[8], bool plain) {
+  uint32_t code[8];
+  if (plain) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) w |= (uint64_t)code[e] << (b * e);
-  if (b == 2) *reinterpret_cast<uint16_t*>(p) = (uint16_t)w;
-  else if (b == 4) *reinterpret_cast<uint32_t*>(p) = (uint32_t)w;
-  else *reinterpret_cast<uint64_t*>(p) = w;
+    for (int e = 0; e < 8; ++e) code[e] = quotient_code(x[e] - mn[e], s[e], r[e], (float)((1 << B) - 1));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) code[e] = (uint32_t)quant_code(x[e], mn[e], s[e], (1 << B) - 1);
+  }
+  put_codes8<B>(p, code);
 }
 
+template <int CTRL>
+__device__ inline float dpp_move(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xF, 0xF, true));
+}
+
+// minimum and maximum over neighbouring lanes: pairs, quads, eights, sixteens
+template <int CTRL>
+__device__ inline void range_step(float& mn, float& mx) {
+  mn = fminf(mn, dpp_move<CTRL>(mn));
+  mx = fmaxf(mx, dpp_move<CTRL>(mx));
+}
+
+__device__ inline float swap_min16(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ inline float swap_min32(float x) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+constexpr int kVRows = 4;  // value rows per lane
+
 // Values, group G >= 8: a group is G/8 neighbouring lanes of one row; its
-// min and max combine by shuffles.  Block = 256 lanes = 256/(D/8) rows.
-__global__ __launch_bounds__(256) void quantize_v_vec_kernel(KSeg seg, const void* __restrict__ v,
-                                                             int dt, int N, int D) {
-  const int cpr = D / 8;  // lanes per row
-  const int c8 = threadIdx.x % cpr;
-  const int r = blockIdx.x * (256 / cpr) + threadIdx.x / cpr, bh = blockIdx.y;
+// min and max combine across lanes.  A block takes kVRows * 256/(D/8) rows.
+template <int DT, int D>
+__device__ inline void quantize_v_block(const KSeg& seg, const void* __restrict__ v, int N, int blk,
+                                        int bh) {
+  constexpr int cpr = D / 8, RB = 256 / cpr;  // lanes per row, rows per pass
+  const int c8 = threadIdx.x % cpr, r0 = blk * (RB * kVRows) + threadIdx.x / cpr;
   const int G = seg.group, lpg = G / 8;
   int b;
   int64_t off;
   const bool ok = head_codes(seg, bh, D, b, off) && !(off & 15);
-  const bool live = r < seg.n_full;
-  float x[8];
-  if (live) {
-    load8(v, dt, ((int64_t)bh * N + r) * D + c8 * 8, x);
-  } else {
+  Raw8<DT> raw[kVRows];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+  for (int i = 0; i < kVRows; ++i) {
+    const int r = min(r0 + i * RB, seg.n_full - 1);  // rows past the end repeat the last
+    raw[i].load(v, ((int64_t)bh * N + r) * D + c8 * 8);
   }
-  float mn = x[0], mx = x[0];
+  uint8_t* codes = const_cast<uint8_t*>(seg.codes_v) + (ok ? off : 0) + c8 * b;
 #pragma unroll
-  for (int e = 1; e < 8; ++e) {
-    mn = fminf(mn, x[e]);
-    mx = fmaxf(mx, x[e]);
-  }
-  // the lanes of a group are aligned and lie in one row, so rows past n_full
-  // only combine among themselves
-  for (int o = 1; o < lpg; o <<= 1) {
-    mn = fminf(mn, __shfl_xor(mn, o, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  }
-  const int qmax = ok ? (1 << b) - 1 : 1;
-  const float s = ok ? __fdiv_rn(mx - mn, (float)qmax) : __builtin_nanf("");
-  if (!live) return;
-  if (c8 % lpg == 0) {
-    const int64_t mi = ((int64_t)bh * seg.cap_full + r) * (D / G) + c8 / lpg;
-    const_cast<float*>(seg.scale_v)[mi] = s;
-    const_cast<float*>(seg.min_v)[mi] = mn;
-  }
-  if (!ok) return;
-  int code[8];
+  for (int i = 0; i < kVRows; ++i) {
+    const int r = r0 + i * RB;
+    float x[8];
+    raw[i].widen(x);
+    float mn = x[0], mx = x[0];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) code[e] = quant_code(x[e], mn, s, qmax);
-  store_codes8(const_cast<uint8_t*>(seg.codes_v) + off + (int64_t)r * (D * b / 8) + c8 * b, code,
-               b);
+    for (int e = 1; e < 8; ++e) {
+      mn = fminf(mn, x[e]);
+      mx = fmaxf(mx, x[e]);
+    }
+    if (lpg > 1) range_step<0xB1>(mn, mx);   // lane ^ 1
+    if (lpg > 2) range_step<0x4E>(mn, mx);   // lane ^ 2
+    if (lpg > 4) range_step<0x141>(mn, mx);  // the other quad of eight
+    if (lpg > 8) range_step<0x140>(mn, mx);  // the other eight of sixteen
+    float s, rs;
+    const bool plain = __all(plain_scale(mx - mn, b, s, rs));
+    if (!plain) s = __fdiv_rn(mx - mn, (float)((1 << b) - 1));
+    if (!ok) s = __builtin_nanf("");
+    const bool live = r < seg.n_full;
+    if (live && c8 % lpg == 0) {
+      const int64_t mi = ((int64_t)bh * seg.cap_full + r) * (D / G) + c8 / lpg;
+      const_cast<float*>(seg.scale_v)[mi] = s;
+      const_cast<float*>(seg.min_v)[mi] = mn;
+    }
+    if (!ok) continue;
+    float mn8[8], s8[8], r8[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      mn8[e] = mn;
+      s8[e] = s;
+      r8[e] = rs;
+    }
+    if (!live) continue;
+    uint8_t* p = codes + (int64_t)r * (D * b / 8);
+    if (b == 4) codes8<4>(p, x, mn8, s8, r8, plain);
+    else if (b == 2) codes8<2>(p, x, mn8, s8, r8, plain);
+    else codes8<8>(p, x, mn8, s8, r8, plain);
+  }
 }
 
 // Keys: one block of 256 lanes per (row group, bh); a lane holds 8 channels
 // of rows rr, rr + RB, ... of the group (RB = 256/(D/8) rows per pass, at
 // most 8 rows per lane since G <= D); per-channel min and max combine over
-// the lanes of a wave by shuffles, then over the four waves through LDS.
-__global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const void* __restrict__ k,
-                                                             int dt, int N, int D) {
-  __shared__ float red[2][4][128];
-  const int cpr = D / 8, RB = 256 / cpr;
+// the lanes of a wave, then over the four waves through LDS.
+template <int DT, int D>
+__device__ inline void quantize_k_block(const KSeg& seg, const void* __restrict__ k, int N, int g,
+                                        int bh, float (&red)[2][4][128]) {
+  constexpr int cpr = D / 8, RB = 256 / cpr, RL = D / RB;
   const int c8 = threadIdx.x % cpr, rr = threadIdx.x / cpr;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int g = blockIdx.x, bh = blockIdx.y, G = seg.group;
+  const int G = seg.group;
   int b;
   int64_t off;
   float* scale = const_cast<float*>(seg.scale_k) + ((int64_t)bh * seg.kgroups + g) * D + c8 * 8;
@@ -210,9 +317,11 @@ __global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const voi
     }
     return;
   }
-  const int qmax = (1 << b) - 1;
   const int64_t base = ((int64_t)bh * N + (int64_t)g * G) * D + c8 * 8;
-  uint4 raw[8];
+  Raw8<DT> raw[RL];
+#pragma unroll
+  for (int i = 0; i < RL; ++i)
+    if (rr + i * RB < G) raw[i].load(k, base + (int64_t)(rr + i * RB) * D);
   float mn[8], mx[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -220,26 +329,21 @@ __global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const voi
     mx[e] = -INFINITY;
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = rr + i * RB;
-    if (r < G) {
-      raw[i] = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(k) + base +
-                                               (int64_t)r * D);
+  for (int i = 0; i < RL; ++i)
+    if (rr + i * RB < G) {
       float x[8];
-      load8(k, dt, base + (int64_t)r * D, x);
+      raw[i].widen(x);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         mn[e] = fminf(mn[e], x[e]);
         mx[e] = fmaxf(mx[e], x[e]);
       }
     }
-  }
-  for (int o = cpr; o < 64; o <<= 1) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      mn[e] = fminf(mn[e], __shfl_xor(mn[e], o, 64));
-      mx[e] = fmaxf(mx[e], __shfl_xor(mx[e], o, 64));
-    }
+  for (int e = 0; e < 8; ++e) {
+    if (cpr == 8) range_step<0x128>(mn[e], mx[e]);  // lane ^ 8: rotation of the row by half
+    mn[e] = swap_min32(swap_min16(mn[e]));
+    mx[e] = -swap_min32(swap_min16(-mx[e]));
   }
   if (lane < cpr) {
 #pragma unroll
@@ -249,7 +353,8 @@ __global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const voi
     }
   }
   __syncthreads();
-  float s[8];
+  float s[8], rs[8], range[8];
+  bool plain = true;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     float a = red[0][0][c8 * 8 + e], z = red[1][0][c8 * 8 + e];
@@ -258,8 +363,16 @@ __global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const voi
       a = fminf(a, red[0][w][c8 * 8 + e]);
       z = fmaxf(z, red[1][w][c8 * 8 + e]);
     }
+    // a channel of NaNs alone: float rows have always left NaN here
+    if (DT == UC_F32 && a > z) a = z = __builtin_nanf("");
     mn[e] = a;
-    s[e] = __fdiv_rn(z - a, (float)qmax);
+    range[e] = z - a;
+    plain &= plain_scale(range[e], b, s[e], rs[e]);
+  }
+  plain = __all(plain);
+  if (!plain) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s[e] = __fdiv_rn(range[e], (float)((1 << b) - 1));
   }
   if (rr == 0) {
 #pragma unroll
@@ -271,22 +384,30 @@ __global__ __launch_bounds__(256) void quantize_k_vec_kernel(KSeg seg, const voi
   const int row_bytes = D * b / 8;
   uint8_t* codes = const_cast<uint8_t*>(seg.codes_k) + off + (int64_t)g * G * row_bytes + c8 * b;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < RL; ++i) {
     const int r = rr + i * RB;
     if (r < G) {
-      const uint32_t u[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
-      int code[8];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint16_t lo = (uint16_t)(u[j] & 0xFFFFu), hi = (uint16_t)(u[j] >> 16);
-        const float x0 = dt == UC_BF16 ? bf16_to_f32(lo) : f16_to_f32(lo);
-        const float x1 = dt == UC_BF16 ? bf16_to_f32(hi) : f16_to_f32(hi);
-        code[2 * j] = quant_code(x0, mn[2 * j], s[2 * j], qmax);
-        code[2 * j + 1] = quant_code(x1, mn[2 * j + 1], s[2 * j + 1], qmax);
-      }
-      store_codes8(codes + (int64_t)r * row_bytes, code, b);
+      float x[8];
+      raw[i].widen(x);
+      uint8_t* p = codes + (int64_t)r * row_bytes;
+      if (b == 4) codes8<4>(p, x, mn, s, rs, plain);
+      else if (b == 2) codes8<2>(p, x, mn, s, rs, plain);
+      else codes8<8>(p, x, mn, s, rs, plain);
     }
   }
+}
+
+// grid (key groups + value blocks, b*h_kv): both halves of a segment in one
+// launch, so that neither waits for the other's last blocks and a small
+// segment pays for one launch.
+template <int DT, int D>
+__global__ __launch_bounds__(256) void quantize_vec_kernel(KSeg seg, const void* __restrict__ k,
+                                                           const void* __restrict__ v, int N,
+                                                           int k_blocks) {
+  __shared__ float red[2][4][128];
+  const int x = blockIdx.x;
+  if (x < k_blocks) quantize_k_block<DT, D>(seg, k, N, x, blockIdx.y, red);
+  else quantize_v_block<DT, D>(seg, v, N, x - k_blocks, blockIdx.y);
 }
 
 // Residual tail: rows n_full..N-1 copied unchanged (16 bytes per lane).
@@ -415,21 +536,21 @@ hipError_t launch_quantize(const uc_shape& sh, const void* k, const void* v, int
                            const KSeg& out, hipStream_t st) {
   const int BH = sh.B * sh.Hkv, D = sh.D;
   if (out.n_full > 0) {
-    // vectorised forms: 2-byte dtypes, head dim 64 or 128, 16-byte aligned
-    // rows (values also need groups of at least 8 channels)
-    const bool vec = dt != UC_F32 && (D == 64 || D == 128) && !((uintptr_t)k & 15) &&
-                     !((uintptr_t)v & 15);
-    if (vec)
-      hipLaunchKernelGGL(quantize_k_vec_kernel, dim3(out.n_full / out.group, BH), dim3(256), 0, st,
-                         out, k, dt, N, D);
-    else
-      hipLaunchKernelGGL(quantize_k_kernel, dim3(out.n_full / out.group, BH), dim3(D), 0, st, out,
-                         k, dt, N, D);
-    if (vec && out.group >= 8) {
-      const int rpb = 256 / (D / 8);
-      hipLaunchKernelGGL(quantize_v_vec_kernel, dim3((out.n_full + rpb - 1) / rpb, BH), dim3(256),
-                         0, st, out, v, dt, N, D);
+    // the vectorised kernel: head dim 64 or 128, 16-byte aligned rows, groups
+    // of at least the 8 channels a lane holds; the others an element per lane
+    const bool vec = (D == 64 || D == 128) && out.group >= 8 && !((uintptr_t)k & 15) && !((uintptr_t)v & 15);
+    const int groups = out.n_full / out.group;
+    if (vec) {
+      const int rows = kVRows * 256 / (D / 8);
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(groups + (out.n_full + rows - 1) / rows, BH), dim3(256), 0,
+                           st, out, k, v, N, groups);
+      };
+      if (dt == UC_F32) D == 64 ? go(quantize_vec_kernel<UC_F32, 64>) : go(quantize_vec_kernel<UC_F32, 128>);
+      else if (dt == UC_F16) D == 64 ? go(quantize_vec_kernel<UC_F16, 64>) : go(quantize_vec_kernel<UC_F16, 128>);
+      else D == 64 ? go(quantize_vec_kernel<UC_BF16, 64>) : go(quantize_vec_kernel<UC_BF16, 128>);
     } else {
+      hipLaunchKernelGGL(quantize_k_kernel, dim3(groups, BH), dim3(D), 0, st, out, k, dt, N, D);
       const int rpb = 256 / D;
       hipLaunchKernelGGL(quantize_v_kernel, dim3((out.n_full + rpb - 1) / rpb, BH), dim3(256), 0,
                          st, out, v, dt, N, D);

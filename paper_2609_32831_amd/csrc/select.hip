@@ -27,7 +27,7 @@ constexpr int kSelThreads = 1024;
 __device__ inline uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f);
   if (u == 0x80000000u) u = 0u;  // -0 ranks as +0
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);  // negative: ~u; positive: above them
 }
 
 constexpr int kSelWaves = kSelThreads / 64;
@@ -46,26 +46,35 @@ __device__ inline uint32_t wave_exclusive(uint32_t x, uint32_t* wave_tot) {
 
 // Radix select finds tau (the k'-th largest order key) 8 bits at a time:
 // each wave counts the keys that match the prefix found so far in a
-// histogram of its own (so hot bins, where scores share an exponent, are
-// contended by 64 lanes only), the 16 histograms are summed, and one wave
-// locates the digit with a scan over the bins from the top.  Compaction:
-// wave w takes the w-th contiguous run of positions, reading 64 consecutive
-// keys at a time; a kept key's output slot is the number of kept keys before
-// it: (keys above tau before it) + min(keys equal to tau before it, need),
-// from ballots within the wave and exclusive sums over the waves.
+// histogram of its own, four copies of each bin in neighbouring banks for the
+// four lanes of a quad (scores share exponents: hot bins are contended by 16
+// lanes only); the histograms are summed, and one wave locates the digit with a
+// scan over the bins from the top.  Compaction: wave w takes the w-th
+// contiguous run of positions, 64 consecutive keys at a time; a kept key's
+// output slot is the number of kept keys before it: (keys above tau before it)
+// + min(keys equal to tau before it, need), from ballots within the wave and
+// exclusive sums over the waves.
+// With KPL > 0 the row (at most KPL * 1024 scores) is read once, every load
+// of a lane in flight together, and held in registers through the four digits
+// and the compaction; with KPL = 0 each pass reads it again.  The passes were
+// bound by one memory latency per 1024 scores: 64 rows of 61440 took 127 us
+// for 16 MB.
 // With k_dev the row count is read from device memory (k = max(*k_dev, 0));
 // k >= N then writes nothing.  Output row stride: keep_ld.
+template <int KPL>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __restrict__ scores, int N,
                                                              int k, int n_recent,
                                                              int32_t* __restrict__ keep,
                                                              const int32_t* __restrict__ k_dev,
                                                              int64_t keep_ld) {
-  __shared__ uint32_t whist[kSelWaves][256];
+  constexpr int kCopies = 4;
+  __shared__ __attribute__((aligned(16))) uint32_t whist[kSelWaves][256 * kCopies];
   __shared__ uint32_t hist[256];
   __shared__ uint32_t wave_tot[kSelWaves];
   __shared__ uint32_t sh_digit, sh_need;
+  static_assert(256 * kCopies == kSelThreads && kCopies == 4, "a thread sums one bin copy, a quad one bin");
   const int bh = blockIdx.x, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (k_dev) {
     k = max(*k_dev, 0);
     if (k >= N) return;  // nothing evicted: the caller keeps its rows
@@ -74,24 +83,60 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
   int32_t* out = keep + (int64_t)bh * keep_ld;
   const int Nc = N - n_recent, kc = k - n_recent;
 
-  uint32_t prefix = 0, need = (uint32_t)kc;
   if (kc > 0) {
+    // the wave's run of positions, whole blocks of 64; past the last score the
+    // key is 0, the lowest there is: such positions follow every real one, so
+    // they never come before a real key equal to tau and are never kept
+    const int per = (Nc + kSelThreads - 1) / kSelThreads * 64;
+    const int i0 = wave * per, i1 = min(i0 + per, Nc);
+    uint32_t held[KPL > 0 ? KPL : 1];
+    if constexpr (KPL > 0) {
+      // a descriptor that ends at the last score: loads past it return 0
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), (short)0, Nc * 4, 0x00020000);
+#pragma unroll
+      for (int j = 0; j < KPL; ++j)
+        held[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (i0 + lane) * 4, 256 * j, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      const int left = Nc - i0 - lane;
+#pragma unroll
+      for (int j = 0; j < KPL; ++j)
+        held[j] = order_key(__uint_as_float(held[j])) & (uint32_t)((64 * j - left) >> 31);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // f(position, key), 64 positions at a time
+    auto each = [&](auto f) {
+      if constexpr (KPL > 0) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // positions formed anew in each pass, not kept beside the keys
+#pragma unroll
+        for (int j = 0; j < KPL; ++j)
+          if (i0 + 64 * j < i1) f(i0 + 64 * j + ln, held[j]);
+      } else {
+        for (int b0 = i0; b0 < i1; b0 += 64) f(b0 + lane, b0 + lane < Nc ? order_key(s[b0 + lane]) : 0u);
+      }
+    };
+    uint32_t prefix = 0, need = (uint32_t)kc;
+#pragma unroll 1
     for (int pass = 0; pass < 4; ++pass) {
       const int shift = 24 - 8 * pass;
       const uint32_t hi_mask = pass == 0 ? 0u : (0xFFFFFFFFu << (32 - 8 * pass));
-      for (int t = lane; t < 256; t += 64) whist[wave][t] = 0u;
-      __syncthreads();
-      for (int i = tid; i < Nc; i += kSelThreads) {
-        const uint32_t key = order_key(s[i]);
-        if ((key & hi_mask) == prefix) atomicAdd(&whist[wave][(key >> shift) & 255u], 1u);
-      }
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t h = 0;
+      uint4* mine = reinterpret_cast<uint4*>(whist[wave]);
 #pragma unroll
-        for (int w = 0; w < kSelWaves; ++w) h += whist[w][tid];
-        hist[tid] = h;
-      }
+      for (int t = 0; t < 256 * kCopies / 4 / 64; ++t) mine[t * 64 + lane] = uint4{0, 0, 0, 0};
+      // the wave's own counts: LDS operations of a wave are in order
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      each([&](int, uint32_t key) {
+        if ((key & hi_mask) == prefix)
+          atomicAdd(&whist[wave][((key >> shift) & 255u) * kCopies + (lane & 3)], 1u);
+      });
+      __syncthreads();
+      uint32_t h = 0;
+#pragma unroll
+      for (int w = 0; w < kSelWaves; ++w) h += whist[w][tid];
+      h += __shfl_xor(h, 1, 64);
+      h += __shfl_xor(h, 2, 64);
+      if ((tid & 3) == 0) hist[tid >> 2] = h;
       __syncthreads();
       if (wave == 0) {
         // lane l owns bins 255-4l .. 252-4l, taken from the top
@@ -120,39 +165,43 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
       __syncthreads();
       prefix |= sh_digit << shift;
       need = sh_need;
-      __syncthreads();
     }
-  }
-  // prefix is the k'-th largest key; `need` rows equal to it are kept
-  if (kc > 0) {
-    const int per = (Nc + kSelWaves - 1) / kSelWaves;
-    const int i0 = min(wave * per, Nc), i1 = min(i0 + per, Nc);
+    // prefix is the k'-th largest key; `need` rows equal to it are kept
     uint32_t cgt = 0, ceq = 0;
-    for (int b0 = i0; b0 < i1; b0 += 64) {
-      const int i = b0 + lane;
-      const uint32_t key = i < i1 ? order_key(s[i]) : 0u;
-      cgt += (uint32_t)__popcll(__ballot(i < i1 && key > prefix));
-      ceq += (uint32_t)__popcll(__ballot(i < i1 && key == prefix));
-    }
+    each([&](int, uint32_t key) {
+      cgt += (uint32_t)__popcll(__ballot(key > prefix));
+      ceq += (uint32_t)__popcll(__ballot(key == prefix));
+    });
     uint32_t gt = wave_exclusive(cgt, wave_tot);
     uint32_t eq = wave_exclusive(ceq, wave_tot);
-    const uint64_t below = (1ull << lane) - 1ull;  // lanes before this one
-    for (int b0 = i0; b0 < i1; b0 += 64) {
-      const int i = b0 + lane;
-      const uint32_t key = i < i1 ? order_key(s[i]) : 0u;
-      const uint64_t bg = __ballot(i < i1 && key > prefix);
-      const uint64_t be = __ballot(i < i1 && key == prefix);
-      const uint32_t g_rank = gt + (uint32_t)__popcll(bg & below);
-      const uint32_t e_rank = eq + (uint32_t)__popcll(be & below);
-      if (i < i1) {
-        if (key > prefix) out[g_rank + min(e_rank, need)] = i;
-        else if (key == prefix && e_rank < need) out[g_rank + e_rank] = i;
-      }
+    each([&](int i, uint32_t key) {
+      const uint64_t bg = __ballot(key > prefix);
+      const uint64_t be = __ballot(key == prefix);
+      // those of the lanes before this one added
+      const uint32_t g_rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, gt));
+      const uint32_t e_rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, eq));
+      if (key > prefix) out[g_rank + min(e_rank, need)] = i;
+      else if (key == prefix && e_rank < need) out[g_rank + e_rank] = i;
       gt += (uint32_t)__popcll(bg);
       eq += (uint32_t)__popcll(be);
-    }
+    });
   }
   for (int j = tid; j < n_recent; j += kSelThreads) out[kc + j] = Nc + j;
+}
+
+// Registers for the row: the smallest that hold it, up to half of the 128 a
+// lane of a 1024-thread workgroup has.
+inline void run_select(int BH, const float* scores, int N, int k, int n_recent, int32_t* keep,
+                       const int32_t* k_dev, int64_t keep_ld, hipStream_t st) {
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(BH), dim3(kSelThreads), 0, st, scores, N, k, n_recent, keep, k_dev, keep_ld);
+  };
+  // a wave's run is ceil(Nc / 16) positions, KPL * 64 at most
+  const int Nc = N - n_recent;
+  if (Nc <= 4 * kSelThreads) go(select_kernel<4>);
+  else if (Nc <= 16 * kSelThreads) go(select_kernel<16>);
+  else if (Nc <= 64 * kSelThreads) go(select_kernel<64>);
+  else go(select_kernel<0>);
 }
 
 // Copy kept rows: 16 bytes per lane; grid.y = (b, h_kv).  Row strides:
@@ -250,8 +299,7 @@ __global__ void append_kernel(const char* knew, const char* vnew, int n_new, cha
 
 hipError_t launch_select(const float* scores, int BH, int N, int k, int n_recent, int32_t* keep,
                          hipStream_t st) {
-  hipLaunchKernelGGL(select_kernel, dim3(BH), dim3(kSelThreads), 0, st, scores, N, k, n_recent,
-                     keep, nullptr, (int64_t)k);
+  run_select(BH, scores, N, k, n_recent, keep, nullptr, (int64_t)k, st);
   return hipGetLastError();
 }
 
@@ -303,8 +351,7 @@ hipError_t launch_evict_step(int BH, int N, const float* scores, const int32_t* 
                              const int32_t* idx_src, void* kdst, void* vdst, int32_t* idx_dst,
                              int64_t dst_ld, int row_bytes, hipStream_t st) {
   if (N == 0) return hipSuccess;  // k >= N whatever k is
-  hipLaunchKernelGGL(select_kernel, dim3(BH), dim3(kSelThreads), 0, st, scores, N, 0, 0, idx_dst,
-                     k_dev, dst_ld);
+  run_select(BH, scores, N, 0, 0, idx_dst, k_dev, dst_ld, st);
   const int64_t lanes = (int64_t)N * (row_bytes / 16);  // grid for k = N - 1 at most
   hipLaunchKernelGGL(gather_kernel, dim3((unsigned)((lanes + 255) / 256), BH), dim3(256), 0, st,
                      (const int32_t*)idx_dst, N, 0, (const char*)ksrc, (const char*)vsrc,

@@ -40,6 +40,11 @@ QCASES = [
     ("f16", 2, 2, 640 + 63, 64, 64, 8),
     ("bf16", 1, 4, 1024 + 5, 128, 128, [8, 2, 4, 8]),
     ("bf16", 1, 1, 48, 128, 16, 2),
+    # float rows; row counts around a block of value rows (64 or 128)
+    ("f32", 1, 2, 128 + 5, 128, 128, 8),
+    ("f32", 2, 1, 65, 128, 8, [2, 4]),
+    ("f32", 1, 1, 129, 64, 64, 2),
+    ("f16", 1, 1, 127, 64, 8, 4),
 ]
 
 
@@ -115,10 +120,40 @@ def test_quantize_constant_and_ramp_groups():
     assert np.all(vcodes[:, :, : G // 2] == 0)
 
 
+def test_quantize_extreme_scales_bit_exact():
+    """Groups whose scale is tiny or huge (outside the range the reciprocal form
+    of the division covers) beside ordinary ones, and quotients at the halves
+    between two codes."""
+    D, G, N = 128, 64, 256
+    rng = np.random.default_rng(8)
+    for bits in (2, 4, 8):
+        k = rng.standard_normal((2, N, D)).astype(np.float32)
+        k[:, :, :8] *= np.float32(2.0**-100)
+        k[:, :, 8:16] *= np.float32(2.0**100)
+        k[:, G:2 * G] = rng.integers(0, 2 * (2**bits - 1) + 1, (2, G, D)).astype(np.float32) / 2 * 0.37
+        k[1, 2 * G:, 16:] *= np.float32(2.0**-120)
+        v = k[:, ::-1].copy()
+        pk = ref.quantize(k, v, "f32", G, [bits] * 2)
+        seg = uc.packed_segment(1, 2, N, D, G, torch.float32, bits=bits)
+        shape = uc.make_shape(1, 2, 2, D)
+        uc.uc_quantize_segment(shape, torch.from_numpy(k).cuda().view(1, 2, N, D),
+                               torch.from_numpy(v).cuda().view(1, 2, N, D), N, seg)
+        torch.cuda.synchronize()
+        n = pk["codes_k"].shape[0]
+        for name in ("codes_k", "codes_v"):
+            assert np.array_equal(seg.t[name].cpu().numpy()[:n], pk[name]), (bits, name)
+        for name in ("scale_k", "min_k", "scale_v", "min_v"):
+            got = seg.t[name].cpu().numpy().reshape(pk[name].shape)
+            assert np.array_equal(got.view(np.uint32), pk[name].view(np.uint32)), (bits, name)
+
+
 # ------------------------------------------------------------------ select
 
 @pytest.mark.parametrize("N,k,nr", [(1, 1, 0), (100, 37, 0), (100, 37, 5), (4099, 1024, 0),
                                     (4099, 4099, 0), (61440, 11735, 0), (300, 10, 10),
+                                    # edges of the row sizes that are held in registers, and past them
+                                    (4096, 50, 0), (16384, 16383, 1), (16385, 3000, 0), (65536, 65, 0),
+                                    (65537, 9000, 7), (66003, 500, 2),
                                     (1500, 0, 0)])
 def test_select_bit_exact(N, k, nr):
     _print_case(test="select", N=N, k=k, n_recent=nr)
