@@ -213,6 +213,13 @@ __device__ inline void codes8(uint8_t* p, const float (&x)[8], const float (&mn)
   put_codes8<B>(p, code);
 }
 
+// minimum and maximum that give NaN if either is NaN: v_minimum3 / v_maximum3
+// take two more values per instruction as they are, where fminf first quiets
+// each operand.  A NaN found so sends the caller to fminf and fmaxf, which
+// drop it.
+__device__ inline float low(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+__device__ inline float high(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 template <int CTRL>
 __device__ inline float dpp_move(float x) {
   return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), CTRL, 0xF, 0xF, true));
@@ -223,15 +230,6 @@ template <int CTRL>
 __device__ inline void range_step(float& mn, float& mx) {
   mn = fminf(mn, dpp_move<CTRL>(mn));
   mx = fmaxf(mx, dpp_move<CTRL>(mx));
-}
-
-__device__ inline float swap_min16(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ inline float swap_min32(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fminf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 constexpr int kVRows = 4;  // value rows per lane
@@ -259,11 +257,18 @@ __device__ inline void quantize_v_block(const KSeg& seg, const void* __restrict_
     const int r = r0 + i * RB;
     float x[8];
     raw[i].widen(x);
-    float mn = x[0], mx = x[0];
+    float mn = low(low(x[0], x[1]), x[2]), mx = high(high(x[0], x[1]), x[2]);
+    mn = low(low(mn, x[3]), x[4]);
+    mx = high(high(mx, x[3]), x[4]);
+    mn = low(low(low(mn, x[5]), x[6]), x[7]);
+    mx = high(high(high(mx, x[5]), x[6]), x[7]);
+    if (__any(mn != mn)) {
+      mn = mx = x[0];
 #pragma unroll
-    for (int e = 1; e < 8; ++e) {
-      mn = fminf(mn, x[e]);
-      mx = fmaxf(mx, x[e]);
+      for (int e = 1; e < 8; ++e) {
+        mn = fminf(mn, x[e]);
+        mx = fmaxf(mx, x[e]);
+      }
     }
     if (lpg > 1) range_step<0xB1>(mn, mx);   // lane ^ 1
     if (lpg > 2) range_step<0x4E>(mn, mx);   // lane ^ 2
@@ -295,26 +300,33 @@ __device__ inline void quantize_v_block(const KSeg& seg, const void* __restrict_
   }
 }
 
+// LDS of a key block: minima and maxima of the lanes that share 8 channels,
+// then the channels' minimum, scale and reciprocal.
+struct KeyLds {
+  float lo[32 * 64], hi[32 * 64];  // [256/(D/8)][D]
+  float mn[128], s[128], rs[128];
+  int plain;
+};
+
 // Keys: one block of 256 lanes per (row group, bh); a lane holds 8 channels
 // of rows rr, rr + RB, ... of the group (RB = 256/(D/8) rows per pass, at
-// most 8 rows per lane since G <= D); per-channel min and max combine over
-// the lanes of a wave, then over the four waves through LDS.
+// most 8 rows per lane since G <= D).  Bound by the vector ALU: the lanes'
+// minima and maxima meet in LDS, where one lane per channel reduces them and
+// forms the scale; done by every lane for its 8 channels, with cross-lane
+// steps, this took half of the block's instructions at G = 64.
 template <int DT, int D>
 __device__ inline void quantize_k_block(const KSeg& seg, const void* __restrict__ k, int N, int g,
-                                        int bh, float (&red)[2][4][128]) {
+                                        int bh, KeyLds& sh) {
   constexpr int cpr = D / 8, RB = 256 / cpr, RL = D / RB;
+  static_assert(RB * D == 32 * 64, "the lanes' minima and maxima fill the array");
   const int c8 = threadIdx.x % cpr, rr = threadIdx.x / cpr;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int G = seg.group;
   int b;
   int64_t off;
-  float* scale = const_cast<float*>(seg.scale_k) + ((int64_t)bh * seg.kgroups + g) * D + c8 * 8;
-  float* mnp = const_cast<float*>(seg.min_k) + ((int64_t)bh * seg.kgroups + g) * D + c8 * 8;
+  float* scale = const_cast<float*>(seg.scale_k) + ((int64_t)bh * seg.kgroups + g) * D;
+  float* mnp = const_cast<float*>(seg.min_k) + ((int64_t)bh * seg.kgroups + g) * D;
   if (!head_codes(seg, bh, D, b, off) || (off & 15)) {  // uniform over the block
-    if (rr == 0) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) scale[e] = __builtin_nanf("");
-    }
+    if (threadIdx.x < D) scale[threadIdx.x] = __builtin_nanf("");
     return;
   }
   const int64_t base = ((int64_t)bh * N + (int64_t)g * G) * D + c8 * 8;
@@ -322,6 +334,7 @@ __device__ inline void quantize_k_block(const KSeg& seg, const void* __restrict_
 #pragma unroll
   for (int i = 0; i < RL; ++i)
     if (rr + i * RB < G) raw[i].load(k, base + (int64_t)(rr + i * RB) * D);
+  if (threadIdx.x == 0) sh.plain = 1;
   float mn[8], mx[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -335,51 +348,67 @@ __device__ inline void quantize_k_block(const KSeg& seg, const void* __restrict_
       raw[i].widen(x);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        mn[e] = fminf(mn[e], x[e]);
-        mx[e] = fmaxf(mx[e], x[e]);
+        mn[e] = low(mn[e], x[e]);
+        mx[e] = high(mx[e], x[e]);
       }
     }
+  bool nan = false;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (cpr == 8) range_step<0x128>(mn[e], mx[e]);  // lane ^ 8: rotation of the row by half
-    mn[e] = swap_min32(swap_min16(mn[e]));
-    mx[e] = -swap_min32(swap_min16(-mx[e]));
-  }
-  if (lane < cpr) {
+  for (int e = 0; e < 8; ++e) nan |= mn[e] != mn[e];
+  if (__any(nan)) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      red[0][wave][c8 * 8 + e] = mn[e];
-      red[1][wave][c8 * 8 + e] = mx[e];
+      mn[e] = INFINITY;
+      mx[e] = -INFINITY;
     }
+#pragma unroll
+    for (int i = 0; i < RL; ++i)
+      if (rr + i * RB < G) {
+        float x[8];
+        raw[i].widen(x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          mn[e] = fminf(mn[e], x[e]);
+          mx[e] = fmaxf(mx[e], x[e]);
+        }
+      }
   }
-  __syncthreads();
-  float s[8], rs[8], range[8];
-  bool plain = true;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    float a = red[0][0][c8 * 8 + e], z = red[1][0][c8 * 8 + e];
+    sh.lo[rr * D + c8 * 8 + e] = mn[e];
+    sh.hi[rr * D + c8 * 8 + e] = mx[e];
+  }
+  __syncthreads();
+  if (threadIdx.x < D) {
+    const int c = threadIdx.x;
+    // no NaN here any more; rows of lanes past the group hold the infinities
+    float a = sh.lo[c], z = sh.hi[c];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      a = fminf(a, red[0][w][c8 * 8 + e]);
-      z = fmaxf(z, red[1][w][c8 * 8 + e]);
+    for (int r = 1; r < RB; ++r) {
+      a = low(a, sh.lo[r * D + c]);
+      z = high(z, sh.hi[r * D + c]);
     }
     // a channel of NaNs alone: float rows have always left NaN here
     if (DT == UC_F32 && a > z) a = z = __builtin_nanf("");
-    mn[e] = a;
-    range[e] = z - a;
-    plain &= plain_scale(range[e], b, s[e], rs[e]);
-  }
-  plain = __all(plain);
-  if (!plain) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = __fdiv_rn(range[e], (float)((1 << b) - 1));
-  }
-  if (rr == 0) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      scale[e] = s[e];
-      mnp[e] = mn[e];
+    float s, r;
+    if (!plain_scale(z - a, b, s, r)) {
+      s = __fdiv_rn(z - a, (float)((1 << b) - 1));
+      sh.plain = 0;
     }
+    sh.mn[c] = a;
+    sh.s[c] = s;
+    sh.rs[c] = r;
+    scale[c] = s;
+    mnp[c] = a;
+  }
+  __syncthreads();
+  const bool plain = sh.plain != 0;
+  float s[8], rs[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    mn[e] = sh.mn[c8 * 8 + e];
+    s[e] = sh.s[c8 * 8 + e];
+    rs[e] = sh.rs[c8 * 8 + e];
   }
   const int row_bytes = D * b / 8;
   uint8_t* codes = const_cast<uint8_t*>(seg.codes_k) + off + (int64_t)g * G * row_bytes + c8 * b;
@@ -404,9 +433,9 @@ template <int DT, int D>
 __global__ __launch_bounds__(256) void quantize_vec_kernel(KSeg seg, const void* __restrict__ k,
                                                            const void* __restrict__ v, int N,
                                                            int k_blocks) {
-  __shared__ float red[2][4][128];
+  __shared__ __attribute__((aligned(16))) KeyLds sh;
   const int x = blockIdx.x;
-  if (x < k_blocks) quantize_k_block<DT, D>(seg, k, N, x, blockIdx.y, red);
+  if (x < k_blocks) quantize_k_block<DT, D>(seg, k, N, x, blockIdx.y, sh);
   else quantize_v_block<DT, D>(seg, v, N, x - k_blocks, blockIdx.y);
 }
 
