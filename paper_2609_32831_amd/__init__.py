@@ -154,6 +154,8 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if torch.cuda.is_initialized():  # the current stream's handle, without a Stream object around it
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         if torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
         return None
@@ -438,10 +440,11 @@ def uc_select_keep(scores: torch.Tensor, k: int, n_recent: int, keep_idx: torch.
     BH, N = scores.shape[0], scores.shape[-1]
     dt = TORCH_DT[k_src.dtype] if k_src is not None else UC_BF16
     D = k_src.shape[-1] if k_src is not None else 128
-    ws = _ws(lib.uc_select_workspace_size(BH, N), scores.device)
+    n_ws = lib.uc_select_workspace_size(BH, N)
+    ws = _ws(n_ws, scores.device) if n_ws else None
     _check(lib.uc_select_keep(scores.data_ptr(), BH, N, k, n_recent, keep_idx.data_ptr(),
                               _ptr(k_src), _ptr(v_src), _ptr(k_dst), _ptr(v_dst), dt, D,
-                              ws.data_ptr(), ws.numel(), _stream(stream)), "uc_select_keep")
+                              _ptr(ws), n_ws, _stream(stream)), "uc_select_keep")
     return keep_idx
 
 
