@@ -85,7 +85,7 @@ def parse():
     return ap.parse_args()
 
 
-DECODE_KERNELS = ("decode_mfma_kernel", "decode_merge_kernel")
+DECODE_KERNELS = ("decode_mfma_kernel", "record_merge_kernel")
 COPY_BYTES = 1 << 30
 
 

@@ -10,8 +10,8 @@
 // codes and scales are reproducible bit for bit.
 //
 // Layout of the output (see unicache.h): row r of a head's codes occupies
-// D*b/8 bytes; channel c sits in byte c*b/8 at bit (c % (8/b))*b.  One lane
-// owns one channel; lanes of one 32-bit word (32/b consecutive channels)
+// D*b/8 bytes; channel c sits in byte c*b/8 at bit (c % (8/b))*b.  In the forms
+// for unaligned rows one lane owns one channel; lanes of one 32-bit word (32/b consecutive channels)
 // OR their shifted codes together with cross-lane shuffles and the first lane
 // of the word stores it, so each row's codes leave as coalesced 32-bit stores.
 #pragma clang fp contract(off)
@@ -428,7 +428,9 @@ __device__ inline void quantize_k_block(const KSeg& seg, const void* __restrict_
 
 // grid (key groups + value blocks, b*h_kv): both halves of a segment in one
 // launch, so that neither waits for the other's last blocks and a small
-// segment pays for one launch.
+// segment pays for one launch.  64 heads of 4096 bf16 rows (176 MB): 60 us, of
+// the vector ALU more than of memory, against 49 + 41 us in two launches; one
+// head of 256 fp32 rows 5 us against 17 + 4.5.
 template <int DT, int D>
 __global__ __launch_bounds__(256) void quantize_vec_kernel(KSeg seg, const void* __restrict__ k,
                                                            const void* __restrict__ v, int N,
