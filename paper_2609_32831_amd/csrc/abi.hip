@@ -260,10 +260,24 @@ size_t wide_bytes(const uc_shape& sh, const KSegs& ks, int M, bool want_o) {
   const size_t chunks = std::min(finest, std::max<size_t>((size_t)wide_wgs(sh, M) + ks.n, coarsest));
   return align256((size_t)sh.B * sh.Hq * M * chunks * (want_o ? sh.D + 2 : 2) * sizeof(float));
 }
-ChunkPlan wide_plan(const uc_shape& sh, const KSegs& ks, int M) {
+// The finest cut whose workgroups are all resident at once: the attention
+// kernel of head dim 128 takes 256 registers and two of its workgroups fit a
+// CU, the others three.  (16 heads over 4673 rows: 592 workgroups of 128 rows
+// were a round of 512 and one of 80, 27.4 us; 416 of 192 rows are one,
+// 23.3 us.)  Longer caches take several rounds whatever the cut: about three
+// workgroups per CU.  Either way at most wide_wgs chunks and one per segment,
+// or the coarsest cut, which is what wide_bytes counts.
+ChunkPlan wide_plan(const uc_shape& sh, const KSegs& ks, int M, bool want_o) {
+  const int wgs = wide_wgs(sh, M);
+  const int resident = sh.D == 128 && want_o ? wgs * 2 / 3 : wgs;
   int64_t total = 0;
   for (int i = 0; i < ks.n; ++i) total += ks.s[i].n_rows;
-  const int64_t per = (total + wide_wgs(sh, M) - 1) / wide_wgs(sh, M);
+  for (int rows = 64; rows <= 256; rows += 64) {
+    int64_t chunks = 0;
+    for (int i = 0; i < ks.n; ++i) chunks += (ks.s[i].n_rows + rows - 1) / rows;
+    if (chunks <= resident) return make_plan(ks, rows, 1 << 30);
+  }
+  const int64_t per = (total + wgs - 1) / wgs;
   return make_plan(ks, (int)std::min<int64_t>((std::max<int64_t>(per, 1) + 63) / 64 * 64, 256), 1 << 30);
 }
 bool wide_path(const uc_shape& sh, int M) { return g_path.load() == UC_PATH_AUTO && wide_ok(sh, M); }
@@ -272,7 +286,7 @@ bool wide_path(const uc_shape& sh, int M) { return g_path.load() == UC_PATH_AUTO
 // (one query block against a long cache), else the coarse one, which many
 // query blocks fill the chip with.
 ChunkPlan attend_plan(const uc_shape& sh, const KSegs& ks, int M) {
-  if (wide_path(sh, M) && wide_bytes(sh, ks, M, true) <= kFineBytes) return wide_plan(sh, ks, M);
+  if (wide_path(sh, M) && wide_bytes(sh, ks, M, true) <= kFineBytes) return wide_plan(sh, ks, M, true);
   return make_plan(ks, kAttRows, kAttMaxChunks);
 }
 size_t attend_ws(const uc_shape& sh, const KSegs& ks, int M) {
@@ -280,7 +294,7 @@ size_t attend_ws(const uc_shape& sh, const KSegs& ks, int M) {
                   std::min(wide_bytes(sh, ks, M, true), kFineBytes));
 }
 ChunkPlan score_lse_plan(const uc_shape& sh, const KSegs& ks, int W) {
-  return wide_path(sh, W) ? wide_plan(sh, ks, W) : make_plan(ks, kLseRows, kLseMaxChunks);
+  return wide_path(sh, W) ? wide_plan(sh, ks, W, false) : make_plan(ks, kLseRows, kLseMaxChunks);
 }
 ChunkPlan score_col_plan(const uc_shape& sh, const KSegs& ks, int W) {
   return make_plan(ks, wide_path(sh, W) ? score_wide_chunk_rows() : 256, 1 << 30);
