@@ -241,9 +241,9 @@ size_t generic_ws(const uc_shape& sh, const KSegs& ks, int rows_min, int max_chu
 // workgroup and 64 to 256 rows: at least a tile per wave; at most 64 rows per
 // wave, so that its running sums keep the length of the vector-ALU kernel's
 // (with 128 the error against 64 bits grew from 3.3e-7 to 4.2e-7).  Between
-// the two, chunks are cut so that about three workgroups per CU exist: fewer
-// left the short calls waiting on one memory latency per tile, more only adds
-// records to merge.  The chunk bound never shrinks as rows are added.
+// the two wide_plan cuts for at most three workgroups per CU: fewer left the
+// short calls waiting on one memory latency per tile, more only adds records
+// to merge.  The chunk bound never shrinks as rows are added.
 int wide_wgs(const uc_shape& sh, int M) {
   const int64_t blocks = ((int64_t)(sh.Hq / sh.Hkv) * M + 15) / 16 * sh.B * sh.Hkv;
   return (int)std::max<int64_t>(1, 3 * device_cus() / blocks);
