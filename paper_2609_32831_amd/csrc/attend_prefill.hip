@@ -739,8 +739,10 @@ bool prefill_mfma_eligible(const uc_shape& sh, const KSegs& segs, int q_dt, int 
 // added.  Measured, 203 query rows of 28 heads on 4 KV heads over 6144 rows (48
 // query blocks), attention kernel alone: 148 us unsplit, 45 with 5 splits, 42
 // with 8, 38 with 10 (the rule), 42 with 16.  Grids that already fill the chip
-// lose: 1792 query blocks (3.5 rounds) 760 us unsplit, 1133 with 16.
-constexpr int kSplitTiles = 8, kMaxSplits = 16;
+// lose: 1792 query blocks (3.5 rounds) 760 us unsplit, 1133 with 16.  Calls
+// over fewer than 32 tiles are not split: a tile takes about 0.77 us, the merge
+// and its records about 8 us, and calls of 24 and 30 us became 6 and 5 % slower.
+constexpr int kSplitTiles = 8, kMinTiles = 32, kMaxSplits = 16;
 
 static int64_t narrow_blocks(const uc_shape& sh, int M) {
   const int64_t nq = (int64_t)(sh.Hq / sh.Hkv) * M;
@@ -748,6 +750,7 @@ static int64_t narrow_blocks(const uc_shape& sh, int M) {
 }
 
 static int prefill_splits(const uc_shape& sh, int tiles, int M) {
+  if (tiles < kMinTiles) return 1;
   const int64_t blocks = narrow_blocks(sh, M);
   const int64_t n = std::min<int64_t>({2 * device_cus() / blocks, tiles / kSplitTiles, kMaxSplits});
   return (int)std::max<int64_t>(n, 1);
