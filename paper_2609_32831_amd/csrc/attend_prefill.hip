@@ -85,6 +85,11 @@ struct Views {
 // record of every query row -- (m, l) in base 2, O, and the log-sum-exp of
 // each segment's rows it saw -- for split_merge_kernel.  Record s of query
 // row r is number r*n + s.  n = 1: outputs are written directly.
+// Every split starts from the reference maximum that an unsplit walk has after
+// its first tile, so a probability is rounded to the same 16 bits however the
+// keys are split (references of the splits' own moved the results of 203 query
+// rows over 6144 by 2.7e-4, as much as that rounding itself); what is left is
+// the order of the sums, and rows whose reference is raised later on.
 struct Split {
   int n, per;
   float* ml;
@@ -148,22 +153,22 @@ struct Stage {
 // global chunk g = tid + i * NT, tile g / 512 of the stage, row (g % 512) / 16,
 // column chunk g % 16 (two rows of one tile with 256 threads, one row of each
 // of two tiles with 512).  F16: V comes from the view's fp16 copy.
-template <bool F16, int NT>
+template <bool F16, int NT, bool V = true>
 __device__ inline void stage_load(const Cursor<F16>& cu, Stage& S, int i) {
   const __amdgpu_buffer_rsrc_t rk = rsrc(cu.k, (uint32_t)cu.n * ROWB);
   const __amdgpu_buffer_rsrc_t rv = rsrc(cu.v, (uint32_t)cu.n * ROWB);
   const int g = (threadIdx.x + i * NT) & 511, r = g >> 4, c = g & 15;
   const int off = (cu.row0 + r) * ROWB + c * 16;
   S.k[i] = bload(rk, off, 0);
-  S.v[i] = bload(rv, off, 0);
+  if (V) S.v[i] = bload(rv, off, 0);
 }
 
 // chunk i into the LDS tile at buf (K rows, V rows at + TILEB)
-template <int NT>
+template <int NT, bool V = true>
 __device__ inline void stage_store(char* buf, const Stage& S, int i) {
   const int g = (threadIdx.x + i * NT) & 511, r = g >> 4, c = g & 15;
   *reinterpret_cast<u4*>(buf + toff(r, c)) = S.k[i];
-  *reinterpret_cast<u4*>(buf + TILEB + toff(r, c)) = S.v[i];
+  if (V) *reinterpret_cast<u4*>(buf + TILEB + toff(r, c)) = S.v[i];
 }
 
 // LDS tile of tile t of the sequence
@@ -197,6 +202,15 @@ __device__ inline float tile_exp(const QState& st, const f4& s0, const f4& s1, f
   return ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
 }
 
+// largest logit of each query column of a tile, in base 2 (the scale is
+// positive, so the maximum of the raw logits gives the maximum)
+__device__ inline float column_max(const float (&p)[8], float scale_log2) {
+  float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])),
+                   fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7]))) * scale_log2;
+  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+  return fmaxf(mx, __shfl_xor(mx, 32, 64));
+}
+
 // rare path: raise the reference to the column maximum, rescale the running
 // state and recompute the probabilities (they stay below 2^kLazy, well inside
 // fp16)
@@ -204,12 +218,7 @@ __device__ inline float tile_raise(QState& st, const f4& s0, const f4& s1, float
                                    float (&e)[8]) {
   float p[8];
   tile_logits(s0, s1, p);
-  // the scale is positive, so the maximum of the raw logits gives the maximum
-  float mx = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])),
-                   fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7]))) * scale_log2;
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  const float m_new = fmaxf(st.m, mx);
+  const float m_new = fmaxf(st.m, column_max(p, scale_log2));
   const float alpha = __builtin_amdgcn_exp2f(st.m - m_new);
   st.l *= alpha;
   st.ls *= alpha;
@@ -385,8 +394,17 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
   constexpr int NT = W * 64;
   Cursor<F16> ct, cs;  // tile t (computed) and the next tile to stage
   Stage SA, SB;
+  // the sequence's first tile, whose maxima a later split starts from, goes to
+  // the last stage (first needed for tile 3)
+  static_assert(!SPLIT || (TPS == 1 && STAGES == 4), "the last stage is free at the start");
+  char* const first = tile_buf<TPS>(lds, STAGES - 1);
   {
     Stage S;
+    if (SPLIT && t_first > 0) {
+      cs.start(vs, bh, 0);
+      stage_load<F16, NT, false>(cs, SA, 0);
+      stage_load<F16, NT, false>(cs, SA, 1);
+    }
     ct.start(vs, bh, t_first);
     cs.start(vs, bh, t_first);
     for (int u = 0; u < 2 * TPS && u < T; ++u) {
@@ -399,6 +417,10 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
         if (TPS == 1 || i == 0) stage_store<NT>(tile_buf<TPS>(lds, u), S, i);
       cs.next(vs, bh);
     }
+    if (SPLIT && t_first > 0) {
+      stage_store<NT, false>(first, SA, 0);
+      stage_store<NT, false>(first, SA, 1);
+    }
     if (TPS == 1 && T > 2) {
       stage_load<F16, NT>(cs, SA, 0);
       stage_load<F16, NT>(cs, SA, 1);
@@ -407,6 +429,17 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
   }
   __syncthreads();
   f4 sc[QT][2];
+  if (SPLIT && t_first > 0) {
+    u4 ka[8];
+    load_ka(first, i16, g4, ka);
+    tile_scores(ka, qop, sc);
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      float p[8];
+      tile_logits(sc[qt][0], sc[qt][1], p);
+      st[qt].m = fmaxf(st[qt].m, column_max(p, scale_log2));
+    }
+  }
   {
     u4 ka[8];
     load_ka(tile_buf<TPS>(lds, 0), i16, g4, ka);
@@ -574,7 +607,8 @@ __global__ __launch_bounds__(W * 64, W == 4 && QT == 2 ? 2 : 1) void prefill_mfm
 
 // One wave per query row: its n records merged into O (each lane two dims),
 // lse and the per-segment lse.  Eight records are loaded at a time, all before
-// any is used; every record holds at least one key tile, so its m is finite.
+// any is used; a record's m is at least the first tile's maximum, so it is
+// finite.
 __global__ __launch_bounds__(256) void split_merge_kernel(int Q, int n, int nseg, Split sp,
                                                           float* __restrict__ o,
                                                           float* __restrict__ lse,

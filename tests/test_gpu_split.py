@@ -53,3 +53,37 @@ def test_split(case):
                 got = sl.cpu().numpy()
                 assert np.array_equal(np.isfinite(got), fin)
                 assert np.allclose(got[fin], sl_ref[fin], rtol=1e-5, atol=1e-4)
+
+
+def test_split_rounds_like_unsplit():
+    """A call with its keys split gives what the unsplit kernel gives for the
+    same rows, up to the order of the sums: three requests one at a time (21
+    query rows of one KV head, split) against the same three in a batch whose
+    query blocks fill the chip (unsplit).  No reference is raised after the
+    first tile: that takes a logit 8 above its maximum in base 2, and these
+    have a standard deviation of 1.4.
+
+    Tolerance: both sum the same products in binary32, 47 tiles of 32 rows one
+    after another or in up to 16 runs merged at the end; a sum of n terms taken
+    in another order moves by about sqrt(n) 2^-24 of the terms' norm, 4e-7
+    here, and the bound is ten times that (probabilities rounded to fp16
+    against other references move the result by 2.7e-4)."""
+    B, Hq, M, n, D = 260, 7, 3, 1500, 128
+    print(f"CASE split_rounding B={B} M={M} n={n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    k, v, q = (torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+               for s in ((B, 1, n, D), (B, 1, n, D), (B, Hq, M, D)))
+
+    def attend(b):
+        x = [t[b].contiguous() for t in (k, v, q)]
+        rows = x[2].shape[0]
+        o = torch.empty(rows, Hq, M, D, device="cuda")
+        uc.uc_attend_mixed(uc.make_shape(rows, Hq, 1, D), [uc.dense_segment(x[0], x[1])], x[2], M, sm_scale(D), o)
+        assert uc.uc_last_kernel() == "prefill_mfma"
+        return o
+
+    whole = attend(slice(0, B))
+    for b in range(3):
+        one = attend(slice(b, b + 1))
+        rel = float((one - whole[b:b + 1]).norm() / whole[b].norm())
+        assert rel <= 4e-6, (b, rel)
