@@ -91,11 +91,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
     const int i0 = wave * per, i1 = min(i0 + per, Nc);
     uint32_t held[KPL > 0 ? KPL : 1];
     if constexpr (KPL > 0) {
-      // a descriptor that ends at the last score: loads past it return 0
+      // a descriptor that ends at the last score: loads past it return 0 (the
+      // whole offset in the operand that is checked against it)
       const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(s), (short)0, Nc * 4, 0x00020000);
 #pragma unroll
       for (int j = 0; j < KPL; ++j)
-        held[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (i0 + lane) * 4, 256 * j, 0);
+        held[j] = __builtin_amdgcn_raw_buffer_load_b32(rs, (i0 + lane) * 4 + 256 * j, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
       const int left = Nc - i0 - lane;
 #pragma unroll
