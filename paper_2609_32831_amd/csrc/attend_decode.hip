@@ -134,9 +134,9 @@ __device__ inline void dense_issue(__amdgpu_buffer_rsrc_t rk, __amdgpu_buffer_rs
   const int i16 = lane & 15, g4 = lane >> 4;
   const int o = (row0 + g4) * ROWB + i16 * 16;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) S.k[i] = bload<kNT>(rk, o, i * 4 * ROWB);
+  for (int i = 0; i < 8; ++i) S.k[i] = bload<kNT>(rk, o + i * 4 * ROWB);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) S.v[i] = bload<kNT>(rv, o, i * 4 * ROWB);
+  for (int i = 0; i < 8; ++i) S.v[i] = bload<kNT>(rv, o + i * 4 * ROWB);
 }
 
 __device__ inline void dense_head(const DenseSet& S, char* lk, char* lv, const char* lq, int lane,
@@ -252,23 +252,23 @@ __device__ inline void packed_issue(const PackedSeg& P, int row0, int lane, Pack
   const int c8 = lane & 15, g4 = lane >> 4;
   constexpr int RB = D * BITS / 8;  // code bytes per row
   const int so = ((row0 >> P.lgG) * D + c8 * 8) * 4;
-  S.sk[0] = bload(P.sk, so, 0);
-  S.sk[1] = bload(P.sk, so, 16);
-  S.mk[0] = bload(P.mk, so, 0);
-  S.mk[1] = bload(P.mk, so, 16);
+  S.sk[0] = bload(P.sk, so);
+  S.sk[1] = bload(P.sk, so + 16);
+  S.mk[0] = bload(P.mk, so);
+  S.mk[1] = bload(P.mk, so + 16);
   const int co = (row0 + g4) * RB + c8 * BITS;
   const int vo = ((row0 + g4) * P.ngv + ((c8 * 8) >> P.lgG)) * 4;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     if constexpr (BITS == 4) {
-      S.ck[i >> 2][i & 3] = bload32<kNT>(P.ck, co, i * 4 * RB);
-      S.cv[i >> 2][i & 3] = bload32<kNT>(P.cv, co, i * 4 * RB);
+      S.ck[i >> 2][i & 3] = bload32<kNT>(P.ck, co + i * 4 * RB);
+      S.cv[i >> 2][i & 3] = bload32<kNT>(P.cv, co + i * 4 * RB);
     } else {
-      S.ck[i >> 2][i & 3] = __builtin_amdgcn_raw_buffer_load_b16(P.ck, co, i * 4 * RB, kNT);
-      S.cv[i >> 2][i & 3] = __builtin_amdgcn_raw_buffer_load_b16(P.cv, co, i * 4 * RB, kNT);
+      S.ck[i >> 2][i & 3] = __builtin_amdgcn_raw_buffer_load_b16(P.ck, co + i * 4 * RB, 0, kNT);
+      S.cv[i >> 2][i & 3] = __builtin_amdgcn_raw_buffer_load_b16(P.cv, co + i * 4 * RB, 0, kNT);
     }
-    S.sv[i >> 2][i & 3] = bload32<kNT>(P.sv, vo, i * 16 * P.ngv);
-    S.mv[i >> 2][i & 3] = bload32<kNT>(P.mv, vo, i * 16 * P.ngv);
+    S.sv[i >> 2][i & 3] = bload32<kNT>(P.sv, vo + i * 16 * P.ngv);
+    S.mv[i >> 2][i & 3] = bload32<kNT>(P.mv, vo + i * 16 * P.ngv);
   }
 }
 
@@ -540,7 +540,7 @@ __device__ __attribute__((always_inline)) inline void decode_body(
     const __amdgpu_buffer_rsrc_t rq = rsrc(q + ((int64_t)b * Hq + hkv * G) * M * D,
                                            (uint32_t)nq * D * 2);
 #pragma unroll
-    for (int t = 0; t < 4; ++t) qop[t] = bload(rq, (i16 * D + t * 32 + g4 * 8) * 2, 0);
+    for (int t = 0; t < 4; ++t) qop[t] = bload(rq, (i16 * D + t * 32 + g4 * 8) * 2);
   }
   // fused append: this call attends the new rows from k_new / v_new (a
   // segment of their own) and stores them into the protected segment for the

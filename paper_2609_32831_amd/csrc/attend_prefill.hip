@@ -159,8 +159,8 @@ __device__ inline void stage_load(const Cursor<F16>& cu, Stage& S, int i) {
   const __amdgpu_buffer_rsrc_t rv = rsrc(cu.v, (uint32_t)cu.n * ROWB);
   const int g = (threadIdx.x + i * NT) & 511, r = g >> 4, c = g & 15;
   const int off = (cu.row0 + r) * ROWB + c * 16;
-  S.k[i] = bload(rk, off, 0);
-  if (V) S.v[i] = bload(rv, off, 0);
+  S.k[i] = bload(rk, off);
+  if (V) S.v[i] = bload(rv, off);
 }
 
 // chunk i into the LDS tile at buf (K rows, V rows at + TILEB)

@@ -111,7 +111,10 @@ __device__ inline void split_p(const float (&e)[8], u4& phi, u4& plo) {
 }
 
 // Raw buffer descriptor over `bytes` bytes from `base`: loads at or past the
-// end return zeros, and each load needs one 32-bit offset register.
+// end return zeros, and each load needs one 32-bit offset register.  Only the
+// vector and immediate offsets are held against the end, so the loads below
+// take no scalar offset: constants of up to 4095 go into the instruction, and
+// what is above into one more register.
 __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
 }
@@ -122,13 +125,13 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void* base, uint32_t bytes) 
 constexpr int kNT = 2;
 
 template <int AUX = 0>
-__device__ inline u4 bload(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
+__device__ inline u4 bload(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX));
 }
 
 template <int AUX = 0>
-__device__ inline uint32_t bload32(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, AUX);
+__device__ inline uint32_t bload32(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, AUX);
 }
 
 // a value the compiler cannot see through (keeps byte-extract conversions)

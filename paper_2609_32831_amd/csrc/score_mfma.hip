@@ -67,8 +67,8 @@ __device__ inline void k_issue(__amdgpu_buffer_rsrc_t rk, int row0, int lane, u4
   const int ko = (row0 + i16) * ROWB + g4 * 16;
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    k[t] = bload(rk, ko, t * 64);
-    k[4 + t] = bload(rk, ko, 16 * ROWB + t * 64);
+    k[t] = bload(rk, ko + t * 64);
+    k[4 + t] = bload(rk, ko + 16 * ROWB + t * 64);
   }
 }
 
@@ -132,8 +132,8 @@ __device__ inline void k_decode_pair(const KSrc& src, int ra, int c0, u4& ka, u4
   const int rb = D * BITS / 8;
   uint64_t wa, wb;
   if (BITS == 4) {
-    wa = bload32(src.rc, ra * rb + c0 / 2, 0);
-    wb = bload32(src.rc, (ra + 16) * rb + c0 / 2, 0);
+    wa = bload32(src.rc, ra * rb + c0 / 2);
+    wb = bload32(src.rc, (ra + 16) * rb + c0 / 2);
   } else if (BITS == 2) {
     wa = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(src.rc, ra * rb + c0 / 4, 0, 0);
     wb = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(src.rc, (ra + 16) * rb + c0 / 4, 0, 0);

@@ -12,7 +12,7 @@ import pytest
 
 from paper_2609_32831_amd import build
 
-SOURCES = ["select.hip"]
+SOURCES = ["select.hip", "attend_decode.hip", "attend_prefill.hip", "score_mfma.hip"]
 
 
 @pytest.mark.parametrize("source", SOURCES)
