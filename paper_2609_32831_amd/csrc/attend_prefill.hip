@@ -177,10 +177,20 @@ __device__ inline char* tile_buf(char* lds, int t) {
   return lds + ((t / TPS) % STAGES) * (TPS * SUBB) + (t % TPS) * SUBB;
 }
 
-// raw logits of one query tile (8 per lane).  Rows past a view's end were
-// staged as zeros (range-checked loads), so their logit is 0 and their V row
-// is 0: they add nothing to O, and tile_step removes what they add to the
-// row sums.
+// rows past a view's end, staged as zeros (range-checked loads), take no part:
+// logit -inf, probability 0 (their V rows are 0 too).  n_valid: rows of the
+// tile.  The lane's rows are formed here, not kept in a register of the loop.
+__device__ inline void tile_mask(f4& s0, f4& s1, int n_valid) {
+  int row = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) / 16 * 4;
+  asm volatile("" : "+v"(row));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (row + j >= n_valid) s0[j] = -INFINITY;
+    if (row + 16 + j >= n_valid) s1[j] = -INFINITY;
+  }
+}
+
+// raw logits of one query tile (8 per lane)
 __device__ inline void tile_logits(const f4& s0, const f4& s1, float (&p)[8]) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -317,8 +327,9 @@ __device__ inline void interleave() {
 // O += V^T P of tile t-1 (operands pp) on the matrix cores, interleaved with
 // the softmax common path of tile t on the vector ALUs; then the rare
 // reference raise (which recomputes tile t's scores from its K rows, still in
-// LDS, so the scores need not stay in registers) and the running sums.  sc
-// holds tile t's scores on entry and tile t+1's on exit; tile t's
+// LDS, so the scores need not stay in registers) and the running sums.  A
+// tile that a view's end leaves partial takes the rare path too, which masks
+// it.  sc holds tile t's scores on entry and tile t+1's on exit; tile t's
 // probability operands go to pn (the caller alternates two sets, so they
 // are never copied).
 template <bool F16, int TPS, bool PV, int QT>
@@ -344,28 +355,22 @@ __device__ __attribute__((always_inline)) inline void tile_step(
   bool rare = false;
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) rare = rare || !(psum[qt] <= kLazyExp);
-  if (__builtin_amdgcn_ballot_w64(rare)) {  // rare: raise the reference max
+  if (n_valid < TILE) rare = true;
+  if (__builtin_amdgcn_ballot_w64(rare)) {  // rare: mask, raise the reference max
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt)
-      if (__builtin_amdgcn_ballot_w64(!(psum[qt] <= kLazyExp))) {
+      if (n_valid < TILE || __builtin_amdgcn_ballot_w64(!(psum[qt] <= kLazyExp))) {
         u4 ka[8];
         load_ka(tile_buf<TPS>(lds, t), i16, g4, ka);
         f4 s0, s1;
         qt_scores(ka, qop[qt], s0, s1);
+        if (n_valid < TILE) tile_mask(s0, s1, n_valid);
         float e[8];
-        psum[qt] = tile_raise(st[qt], s0, s1, scale_log2, e);
+        psum[qt] = tile_exp(st[qt], s0, s1, scale_log2, e);
+        if (__builtin_amdgcn_ballot_w64(!(psum[qt] <= kLazyExp)))
+          psum[qt] = tile_raise(st[qt], s0, s1, scale_log2, e);
         pn[qt] = pack_p<F16>(e);
       }
-  }
-  if (n_valid < TILE) {
-    // the TILE - n_valid rows past the view's end each added 2^-m to their
-    // column's sum (logit 0); a quarter of that comes off each of the
-    // column's four lanes.  The fp16 bound above counted them, so their
-    // probability operands stay in range too.
-    const float gone = 0.25f * (float)(TILE - n_valid);
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-      psum[qt] = fmaf(-gone, __builtin_amdgcn_exp2f(-st[qt].m), psum[qt]);
   }
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
@@ -436,6 +441,7 @@ __device__ __attribute__((always_inline)) inline int tile_loop(
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
       float p[8];
+      tile_mask(sc[qt][0], sc[qt][1], vs.v[0].n);
       tile_logits(sc[qt][0], sc[qt][1], p);
       st[qt].m = fmaxf(st[qt].m, column_max(p, scale_log2));
     }
