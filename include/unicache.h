@@ -45,7 +45,8 @@
  *   error nothing is written and no work is enqueued.  UC_E_INVALID covers
  *   bad sizes, null required pointers and misaligned pointers,
  *   UC_E_UNSUPPORTED a legal but unimplemented combination, UC_E_WORKSPACE
- *   a workspace smaller than the matching *_workspace_size helper reports,
+ *   a workspace too small for the call (one of the size that the matching
+ *   *_workspace_size helper reports never is),
  *   UC_E_DEVICE a HIP error reported at launch.  uc_last_error() returns a
  *   thread-local text describing the last failure of the calling thread.
  * - Values stored in device memory (codes, per-head bit widths, offsets)
@@ -330,7 +331,12 @@ uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_segment* segs,
 
 /* Workspace bytes for uc_attend_mixed.  The value never decreases when a
  * segment gains rows, so a workspace sized for the largest row counts (say a
- * decode tail at full capacity) serves every call with fewer rows. */
+ * decode tail at full capacity) serves every call with fewer rows.  One sized
+ * for the largest M serves every smaller M of the same kernel path too, though
+ * the size reported for that M may be larger (short calls keep more partial
+ * results where there is room for them; with less the result is the same up to
+ * the order of the sums and, on the bf16 path, the rounding of probabilities
+ * to 16 bits). */
 size_t uc_attend_workspace_size(const uc_shape* shape, const uc_segment* segs,
                                 int n_segs, uc_dtype q_dt, int M);
 

@@ -283,15 +283,27 @@ ChunkPlan wide_plan(const uc_shape& sh, const KSegs& ks, int M, bool want_o) {
 bool wide_path(const uc_shape& sh, int M) { return g_path.load() == UC_PATH_AUTO && wide_ok(sh, M); }
 
 // Attention outside the bf16 kernels: the fine cut when its records are few
-// (one query block against a long cache), else the coarse one, which many
-// query blocks fill the chip with.
-ChunkPlan attend_plan(const uc_shape& sh, const KSegs& ks, int M) {
-  if (wide_path(sh, M) && wide_bytes(sh, ks, M, true) <= kFineBytes) return wide_plan(sh, ks, M, true);
+// (one query block against a long cache) and the workspace holds them, else
+// the coarse one, which many query blocks fill the chip with.
+ChunkPlan attend_plan(const uc_shape& sh, const KSegs& ks, int M, size_t ws_bytes) {
+  if (wide_path(sh, M) && wide_bytes(sh, ks, M, true) <= std::min(kFineBytes, ws_bytes))
+    return wide_plan(sh, ks, M, true);
   return make_plan(ks, kAttRows, kAttMaxChunks);
 }
 size_t attend_ws(const uc_shape& sh, const KSegs& ks, int M) {
   return std::max(generic_ws(sh, ks, kAttRows, kAttMaxChunks, M, true),
                   std::min(wide_bytes(sh, ks, M, true), kFineBytes));
+}
+// The smallest workspace that a call runs in.  The size reported to callers
+// holds the records of a finer cut of the keys too; those shrink where more
+// query rows leave less to cut, so a workspace sized at the largest M may hold
+// fewer, and then the call is cut more coarsely instead of being refused.
+size_t attend_least_ws(const uc_shape& sh, const KSegs& ks, int q_dt, int M) {
+  if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(sh, ks, q_dt, M))
+    return decode_mfma_workspace(sh, ks, M);
+  if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(sh, ks, q_dt, M))
+    return prefill_mfma_min_workspace(sh, ks);
+  return generic_ws(sh, ks, kAttRows, kAttMaxChunks, M, true);
 }
 ChunkPlan score_lse_plan(const uc_shape& sh, const KSegs& ks, int W) {
   return wide_path(sh, W) ? wide_plan(sh, ks, W, false) : make_plan(ks, kLseRows, kLseMaxChunks);
@@ -356,12 +368,9 @@ size_t uc_attend_workspace_size(const uc_shape* shape, const uc_segment* segs, i
   return attend_ws(*shape, ks, M);
 }
 
-// fit: run in ws_bytes even if the reported size is larger, as long as the
-// call can (multi-query calls then cut their keys into fewer splits)
-static uc_status attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
-                              const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
-                              float* lse, float* seg_lse, void* ws, size_t ws_bytes, bool fit,
-                              void* stream) {
+uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
+                          const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
+                          float* lse, float* seg_lse, void* ws, size_t ws_bytes, void* stream) {
   TimerScope timer;
   KSegs ks;
   uc_status st = check_segments(shape, segs, n_segs, ks);
@@ -372,23 +381,18 @@ static uc_status attend_mixed(const uc_shape* shape, const uc_segment* segs, int
   if (!(sm_scale > 0.0f) || !isfinite(sm_scale)) return fail(UC_E_INVALID, "sm_scale must be finite and > 0");
   if ((int64_t)shape->B * shape->Hq * M > INT32_MAX) return fail(UC_E_UNSUPPORTED, "too many query rows");
   hipStream_t s = (hipStream_t)stream;
+  const size_t need = attend_least_ws(*shape, ks, q_dt, M);
+  if (ws_bytes < need || (need && !ws))
+    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(*shape, ks, q_dt, M)) {
-    const size_t need = decode_mfma_workspace(*shape, ks, M);
-    if (ws_bytes < need || (need && !ws))
-      return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
     g_last_kernel = "decode_mfma";
     return launched(launch_decode_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, s));
   }
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M)) {
-    const size_t need = fit ? prefill_mfma_min_workspace(*shape, ks) : prefill_mfma_workspace(*shape, ks, M);
-    if (ws_bytes < need || (need && !ws))
-      return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
     g_last_kernel = "prefill_mfma";
     return launched(launch_prefill_mfma(*shape, ks, q, M, sm_scale, o, lse, seg_lse, ws, ws_bytes, s));
   }
-  const ChunkPlan p = attend_plan(*shape, ks, M);
-  const size_t need = attend_ws(*shape, ks, M);
-  if (ws_bytes < need || !ws) return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  const ChunkPlan p = attend_plan(*shape, ks, M, ws_bytes);
   float* partial = (float*)ws;
   g_last_kernel = "attend_valu";
   hipError_t e = kernel_timer_begin(s);
@@ -401,13 +405,6 @@ static uc_status attend_mixed(const uc_shape* shape, const uc_segment* segs, int
     e = seg_lse ? launch_attend_combine(*shape, ks, p, M, partial, o, lse, seg_lse, s)
                 : launch_record_merge(shape->D, shape->B * shape->Hq * M, p.n_chunks, partial, o, lse, s);
   return launched(e);
-}
-
-uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_segs,
-                          const void* q, uc_dtype q_dt, int M, float sm_scale, float* o,
-                          float* lse, float* seg_lse, void* ws, size_t ws_bytes, void* stream) {
-  return attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws, ws_bytes,
-                      false, stream);
 }
 
 // ---------------------------------------------------------------- allocation-free attention
@@ -448,9 +445,7 @@ extern "C" uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_seg
   uc_status st = check_segments(shape, segs, n_segs, ks);
   if (st) return st;
   if (M < 1 || !dtype_ok(q_dt)) return fail(UC_E_INVALID, "bad M (%d) or q dtype (%d)", M, q_dt);
-  const bool prefill = g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, ks, q_dt, M);
-  const size_t need = prefill ? prefill_mfma_min_workspace(*shape, ks)
-                              : uc_attend_workspace_size(shape, segs, n_segs, q_dt, M);
+  const size_t need = attend_least_ws(*shape, ks, q_dt, M);
   if (need > UC_SCRATCH_BYTES)
     return fail(UC_E_UNSUPPORTED,
                 "this call needs %zu bytes of scratch, above the %u-byte static array; use "
@@ -458,8 +453,8 @@ extern "C" uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_seg
   void* ws = nullptr;
   st = scratch_address(&ws);
   if (st) return st;
-  return attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws,
-                      UC_SCRATCH_BYTES, true, stream);
+  return uc_attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws,
+                         UC_SCRATCH_BYTES, stream);
 }
 
 // ---------------------------------------------------------------- decode step, append fused
@@ -500,7 +495,7 @@ uc_status uc_attend_append(const uc_shape* shape, const uc_segment* segs, int n_
                      decode_mfma_eligible(*shape, ks, q_dt, M);
   if (!fused) {
     // the two calls this one stands for, checked before either is enqueued
-    const size_t need = uc_attend_workspace_size(shape, after, n_segs, q_dt, M);
+    const size_t need = attend_least_ws(*shape, ks, q_dt, M);
     if (ws_bytes < need || (need && !ws)) return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
     if (n_new > 0) {
       KSeg t = ks.s[tail];

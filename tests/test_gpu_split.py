@@ -87,3 +87,28 @@ def test_split_rounds_like_unsplit():
         one = attend(slice(b, b + 1))
         rel = float((one - whole[b:b + 1]).norm() / whole[b].norm())
         assert rel <= 4e-6, (b, rel)
+
+
+@pytest.mark.parametrize("dtype,D,heads,n,large,small", [
+    ("bf16", 128, (28, 4), 8192, 4096, 40),  # unsplit at 4096 query rows, split at 40
+    ("f32", 64, (1, 1), 49152, 17, 16),       # two query blocks, then one with more records per row
+], ids=["prefill", "wide"])
+def test_workspace_of_the_largest_query_block(dtype, D, heads, n, large, small):
+    """A workspace sized for the largest query block serves a smaller one,
+    whose own reported size is larger."""
+    Hq, Hkv = heads
+    print(f"CASE workspace_largest {dtype} {heads} {large} {small}", flush=True)
+    k, v = (rand_rows(s, Hkv, n, D, dtype) for s in (1, 2))
+    segs = [uc.dense_segment(dev(k, dtype).view(1, Hkv, n, D), dev(v, dtype).view(1, Hkv, n, D))]
+    shape, sm = uc.make_shape(1, Hq, Hkv, D), sm_scale(D)
+    have, want = (uc.uc_attend_workspace_size(shape, segs, uc.NAME_DT[dtype], m) for m in (large, small))
+    assert have < want
+    q = rand_rows(3, Hq, small, D, dtype).reshape(1, Hq, small, D)
+    o_ref = ref.attend(ref.widen(q, dtype), ref.widen(k, dtype)[None], ref.widen(v, dtype)[None], None,
+                       np.zeros(n, np.int32), 1, sm)[0]
+    for size in (have, want):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        o = torch.empty(1, Hq, small, D, device="cuda")
+        uc.uc_attend_mixed(shape, segs, dev(q, dtype), small, sm, o, ws=ws)
+        torch.cuda.synchronize()
+        check_attention(o.cpu().numpy(), o_ref, f"{size} bytes")
