@@ -417,13 +417,17 @@ size_t uc_plan_workspace_size(uc_plan plan);
 int uc_plan_tail_rows(uc_plan plan);
 /* Attention over the plan's segments as they stand: the result of
  * uc_attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse,
- * ws, ws_bytes, stream).  On the multi-query matrix-core path ((Hq/Hkv)*M >
+ * ws, ws_bytes, stream) (a multi-query call with few query rows splits the
+ * keys there and not here: then the same up to the order of the sums and the
+ * rounding of probabilities to 16 bits).  On the multi-query matrix-core path ((Hq/Hkv)*M >
  * 16) the first call with a given ws also prepares it -- packed rows
  * dequantised, V converted to fp16, the range flag -- and later calls with
  * the same ws reuse that preparation (App. E: packed KV dequantised into a
  * reusable workspace), so between them the segments' contents and ws must
  * not change: after writing to a segment (re-quantisation, appended rows
  * outside the plan) or using ws for other calls, call uc_plan_invalidate.
+ * Calls that reuse a preparation only read ws, so they may overlap on several
+ * streams once the preparing call has finished; every other call writes ws.
  * ws: at least uc_plan_workspace_size bytes. */
 uc_status uc_plan_attend(uc_plan plan, const void* q, float* o, float* lse,
                          float* seg_lse, void* ws, size_t ws_bytes,

@@ -29,9 +29,9 @@ hipError_t launch_prefill_mfma(const uc_shape& sh, const KSegs& segs, const void
                                size_t ws_bytes, hipStream_t st);
 hipError_t launch_prefill_prepare(const uc_shape& sh, const KSegs& segs, void* ws, hipStream_t st,
                                   void* views_out);
-hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void* views,
-                              const void* q, int M, float sm_scale, float* o, float* lse,
-                              float* seg_lse, void* ws, size_t ws_bytes, hipStream_t st);
+hipError_t launch_prefill_run(const uc_shape& sh, int n_segs, const void* views, const void* q,
+                              int M, float sm_scale, float* o, float* lse, float* seg_lse,
+                              const void* ws, void* rec, size_t rec_bytes, hipStream_t st);
 int score_mfma_chunk_rows();
 int64_t score_mfma_col_slots(int64_t base);
 hipError_t launch_score_lse_mfma(const uc_shape& sh, const KSegs& segs, const ChunkPlan& plan,
@@ -583,7 +583,7 @@ uc_status uc_plan_create(const uc_shape* shape, const uc_segment* segs, int n_se
   check_segments(shape, full, n_segs, kf);
   size_t need;
   if (g_path.load() == UC_PATH_AUTO && prefill_mfma_eligible(*shape, kf, q_dt, M)) {
-    need = prefill_mfma_workspace(*shape, kf, M);
+    need = prefill_mfma_min_workspace(*shape, kf);
   } else {
     need = attend_ws(*shape, kf, M);
     if (g_path.load() == UC_PATH_AUTO && decode_mfma_eligible(*shape, kf, q_dt, M))
@@ -625,9 +625,11 @@ uc_status uc_plan_attend(uc_plan plan, const void* q, float* o, float* lse, floa
     if (e != hipSuccess) return launched(e);
     plan->prepared_ws = ws;
   }
+  // no key splits here: their records would be written into a workspace that
+  // calls on other streams, or replays of a captured call, may be reading
   g_last_kernel = "prefill_mfma";
-  return launched(launch_prefill_run(sh, plan->ks, plan->views, q, plan->M, plan->sm_scale, o, lse,
-                                     seg_lse, ws, ws_bytes, s));
+  return launched(launch_prefill_run(sh, plan->n_segs, plan->views, q, plan->M, plan->sm_scale, o,
+                                     lse, seg_lse, ws, nullptr, 0, s));
 }
 
 uc_status uc_plan_attend_append(uc_plan plan, const void* k_new, const void* v_new, int n_new,

@@ -878,15 +878,15 @@ hipError_t launch_prefill_prepare(const uc_shape& sh, const KSegs& segs, void* w
   return hipGetLastError();
 }
 
-// The attention kernel over prepared views (launch_prefill_prepare on the
-// same ws).  ws_bytes: at least prefill_mfma_min_workspace; the key splits
-// take what is there beyond it.
-hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void* views,
-                              const void* q, int M, float sm_scale, float* o, float* lse,
-                              float* seg_lse, void* ws, size_t ws_bytes, hipStream_t st) {
+// The attention kernel over prepared views (launch_prefill_prepare on ws, which
+// is only read here).  The records of key splits take rec_bytes at rec: without
+// room for two splits there are none.
+hipError_t launch_prefill_run(const uc_shape& sh, int n_segs, const void* views, const void* q,
+                              int M, float sm_scale, float* o, float* lse, float* seg_lse,
+                              const void* ws, void* rec, size_t rec_bytes, hipStream_t st) {
   Views vs;
   memcpy(&vs, views, sizeof vs);
-  const int BH = sh.B * sh.Hkv, n_segs = segs.n;
+  const int BH = sh.B * sh.Hkv;
   const uint32_t* flags = (const uint32_t*)ws;
   hipError_t e;
   const int nq = (sh.Hq / sh.Hkv) * M;
@@ -900,14 +900,13 @@ hipError_t launch_prefill_run(const uc_shape& sh, const KSegs& segs, const void*
   const int n_qblocks = (nq + qr - 1) / qr;
   Split sp{1, vs.tiles, nullptr, nullptr, nullptr};
   if (!wide) {
-    const size_t min = prefill_mfma_min_workspace(sh, segs);
-    const size_t room = (ws_bytes - min) / split_bytes(sh, M, n_segs);
+    const size_t room = rec_bytes / split_bytes(sh, M, n_segs);
     const int n = (int)std::min<size_t>(prefill_splits(sh, vs.tiles, M), room);
     if (n > 1) {
       sp.per = (vs.tiles + n - 1) / n;
       sp.n = (vs.tiles + sp.per - 1) / sp.per;
       const int64_t recs = (int64_t)sh.B * sh.Hq * M * sp.n;
-      sp.o = (float*)((char*)ws + min);
+      sp.o = (float*)rec;
       sp.ml = sp.o + recs * D;
       sp.seg = sp.ml + recs * 2;
     }
@@ -940,7 +939,9 @@ hipError_t launch_prefill_mfma(const uc_shape& sh, const KSegs& segs, const void
   alignas(16) char views[kPrefillViewBytes];
   const hipError_t e = launch_prefill_prepare(sh, segs, ws, st, views);
   if (e != hipSuccess) return e;
-  return launch_prefill_run(sh, segs, views, q, M, sm_scale, o, lse, seg_lse, ws, ws_bytes, st);
+  const size_t min = prefill_mfma_min_workspace(sh, segs);
+  return launch_prefill_run(sh, segs.n, views, q, M, sm_scale, o, lse, seg_lse, ws, (char*)ws + min,
+                            ws_bytes - min, st);
 }
 
 }  // namespace uc

@@ -18,6 +18,7 @@ if not torch.cuda.is_available():
 import oracle as ref  # noqa: E402
 import paper_2609_32831_amd as uc  # noqa: E402
 from gpu_util import check_attention, dev, packed_from_oracle, rand_rows, sm_scale  # noqa: E402
+from gpu_util import host_bytes as host  # noqa: E402
 
 D = 128
 
@@ -113,3 +114,37 @@ def test_plan_attend_matches_attend_mixed(M, path, kernel):
         plan.close()
     finally:
         uc.uc_set_path(prev)
+
+
+def test_prepared_plan_only_reads_its_workspace():
+    """Multi-query attention on a prepared plan leaves the workspace as it is
+    (several streams may run it at once), also for few query rows over a long
+    context, where uc_attend_mixed keeps the partial results of its key splits
+    there; two streams give what one gives."""
+    B, Hq, Hkv, M, n = 1, 28, 4, 40, 2048
+    print(f"CASE plan_reads_ws M={M} n={n}", flush=True)
+    shape, sm = uc.make_shape(B, Hq, Hkv, D), sm_scale(D)
+    k, v = (dev(rand_rows(s, B * Hkv, n, D, "bf16"), "bf16").reshape(B, Hkv, n, D) for s in (1, 2))
+    segs = [uc.dense_segment(k, v)]
+    plan = uc.AttendPlan(shape, segs, None, torch.bfloat16, M, sm)
+    q = [dev(rand_rows(60 + i, B * Hq, M, D, "bf16").reshape(B, Hq, M, D), "bf16") for i in range(2)]
+    want = [torch.empty(B, Hq, M, D, device="cuda") for _ in q]
+    plan.attend(q[0], want[0])
+    torch.cuda.synchronize()
+    before = plan.ws.clone()
+    plan.attend(q[1], want[1])
+    torch.cuda.synchronize()
+    assert torch.equal(plan.ws, before)
+    streams = [torch.cuda.Stream() for _ in q]
+    got = [[torch.empty_like(want[0]) for _ in range(8)] for _ in q]
+    for i in range(8):
+        for s, x, o in zip(streams, q, got):
+            plan.attend(x, o[i], stream=s)
+    torch.cuda.synchronize()
+    for o, w in zip(got, want):
+        for x in o:
+            assert torch.equal(x, w)
+    o_ref = ref.attend(ref.widen(host(q[1]), "bf16"), ref.widen(host(k), "bf16"), ref.widen(host(v), "bf16"), None,
+                       np.zeros(n, np.int32), 1, sm)[0]
+    check_attention(want[1].cpu().numpy(), o_ref, "plan")
+    plan.close()
