@@ -310,15 +310,14 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs,
 
 /* uc_attend_mixed for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
- * the same computation, kernels and results (a multi-query call whose key
- * splits do not all fit the array takes fewer of them: the same up to the
- * order of floating-point sums), with the workspace taken from
- * a static device array of UC_SCRATCH_BYTES bytes that the library holds on
- * every GPU it runs on until the process ends.  The call allocates nothing
+ * the same computation, kernels and results, with the workspace taken from
+ * a static device array that the library holds on every GPU it runs on until
+ * the process ends (UC_SCRATCH_BYTES, and 35 MB for the partial results of
+ * calls that split their keys).  The call allocates nothing
  * (no hipMalloc, no allocating library routine); the caller still passes q,
- * o and the optional lse / seg_lse.  A call whose uc_attend_workspace_size
- * (without the records of key splits) exceeds UC_SCRATCH_BYTES (large prefill
- * blocks over packed segments) fails with UC_E_UNSUPPORTED before any launch.  Every call on one GPU shares
+ * o and the optional lse / seg_lse.  A call that needs more than
+ * UC_SCRATCH_BYTES without those partial results (large prefill blocks over
+ * packed segments) fails with UC_E_UNSUPPORTED before any launch.  Every call on one GPU shares
  * that GPU's array: calls that may overlap on one GPU (different streams
  * without ordering between them) race and must not be issued; calls ordered
  * on one stream are safe.  The array's contents are not preserved between

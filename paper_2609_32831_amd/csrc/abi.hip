@@ -408,11 +408,13 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_s
 }
 
 // ---------------------------------------------------------------- allocation-free attention
-// One file-scope scratch array per GPU, in place of the caller's workspace.
+// One file-scope scratch array per GPU, in place of the caller's workspace,
+// with room for the records of key splits beyond the size that a call is
+// admitted by, so that every call runs as it does with a workspace of its own.
 // The host takes its device address once per device with that device current
 // and uses only that address afterwards (the array's name is a host-side
 // stand-in in host code).
-static __device__ __align__(256) unsigned char scratch[UC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[UC_SCRATCH_BYTES + kSplitRecordBytes];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -454,7 +456,7 @@ extern "C" uc_status uc_attend_mixed_noalloc(const uc_shape* shape, const uc_seg
   st = scratch_address(&ws);
   if (st) return st;
   return uc_attend_mixed(shape, segs, n_segs, q, q_dt, M, sm_scale, o, lse, seg_lse, ws,
-                         UC_SCRATCH_BYTES, stream);
+                         sizeof scratch, stream);
 }
 
 // ---------------------------------------------------------------- decode step, append fused

@@ -12,6 +12,11 @@ namespace uc {
 constexpr int kMaxSeg = UC_MAX_SEGMENTS;
 // bytes that hold the prepared views of one multi-query attention call
 constexpr size_t kPrefillViewBytes = 1024;
+// most that the records of one multi-query call's key splits take: a split call
+// has at most two 128-row query blocks per compute unit in all, each row with
+// (m, l), O and a log-sum-exp per segment (chips have up to 256 units; a larger
+// one would find room for fewer splits)
+constexpr size_t kSplitRecordBytes = (size_t)2 * 256 * 128 * (2 + 128 + UC_MAX_SEGMENTS) * 4 + 256;
 
 // compute units of the current device (cached after the first call)
 int device_cus();
