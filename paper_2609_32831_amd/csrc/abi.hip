@@ -621,6 +621,9 @@ uc_status uc_plan_attend(uc_plan plan, const void* q, float* o, float* lse, floa
     return uc_attend_mixed(&sh, plan->segs, plan->n_segs, q, plan->q_dt, plan->M, plan->sm_scale,
                            o, lse, seg_lse, ws, ws_bytes, stream);
   }
+  // ws_need is that of the path selected at creation
+  const size_t need = attend_least_ws(sh, plan->ks, plan->q_dt, plan->M);
+  if (ws_bytes < need) return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   hipStream_t s = (hipStream_t)stream;
   if (plan->prepared_ws != ws) {
     const hipError_t e = launch_prefill_prepare(sh, plan->ks, ws, s, plan->views);
@@ -666,6 +669,9 @@ uc_status uc_plan_attend_append(uc_plan plan, const void* k_new, const void* v_n
     nk.row_stride = n_new;
     nk.k = k_new;
     nk.v = v_new;
+    // ws_need is that of the path selected at creation
+    const size_t need = attend_least_ws(sh, plan->ks, plan->q_dt, plan->M);
+    if (ws_bytes < need) return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
     AppendOp ap{(const char*)k_new, (const char*)v_new, (char*)ks.s[tail].k, (char*)ks.s[tail].v,
                 n_new, ks.s[tail].row_stride, pos, sh.D * dtype_bytes(nk.dtype)};
     g_last_kernel = "decode_mfma_append";

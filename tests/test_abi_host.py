@@ -277,6 +277,33 @@ def test_plan_validation(uc):
     assert create(segs, -2)[0] == E
 
 
+@pytest.mark.parametrize("M,rows", [(17, 20000), (1, 64)], ids=["multi-query", "decode"])
+def test_plan_workspace_after_a_path_switch(uc, M, rows):
+    """A plan made while the vector-ALU path was selected reports that path's
+    workspace; on the matrix-core path, which needs more, its calls are refused
+    instead of running past it."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would launch on made-up addresses if the check were missing")
+    sh, L, h = uc.uc_shape(1, 4, 1, 128), uc.lib, ctypes.c_void_p()
+    segs = (uc.uc_segment * 2)(_dense(uc, rows), _dense(uc, 7, stride=8))
+    prev = uc.uc_set_path(uc.UC_PATH_VALU)
+    try:
+        assert L.uc_plan_create(ctypes.byref(sh), segs, 2, 1, uc.UC_BF16, M, ctypes.c_float(0.1),
+                                ctypes.byref(h)) == uc.UC_OK
+    finally:
+        uc.uc_set_path(prev)
+    try:
+        have = L.uc_plan_workspace_size(h)
+        assert have < L.uc_attend_workspace_size(ctypes.byref(sh), segs, 2, uc.UC_BF16, M)
+        assert L.uc_plan_attend(h, FAKE, FAKE, None, None, FAKE, have, None) == uc.UC_E_WORKSPACE
+        assert L.uc_plan_attend_append(h, FAKE, FAKE, 1, FAKE, FAKE, None, FAKE, have,
+                                       None) == uc.UC_E_WORKSPACE
+        assert L.uc_plan_tail_rows(h) == 7
+    finally:
+        L.uc_plan_destroy(h)
+
+
 def test_dynamic_budget_entry_validation(uc):
     sh = uc.uc_shape(1, 4, 2, 128)
     dense = _dense(uc, 64)
