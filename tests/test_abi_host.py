@@ -277,7 +277,7 @@ def test_plan_validation(uc):
     assert create(segs, -2)[0] == E
 
 
-@pytest.mark.parametrize("M,rows", [(17, 20000), (1, 64)], ids=["multi-query", "decode"])
+@pytest.mark.parametrize("M,rows", [(17, 100000), (1, 64)], ids=["multi-query", "decode"])
 def test_plan_workspace_after_a_path_switch(uc, M, rows):
     """A plan made while the vector-ALU path was selected reports that path's
     workspace; on the matrix-core path, which needs more, its calls are refused
