@@ -305,9 +305,6 @@ size_t attend_least_ws(const uc_shape& sh, const KSegs& ks, int q_dt, int M) {
     return prefill_mfma_min_workspace(sh, ks);
   return generic_ws(sh, ks, kAttRows, kAttMaxChunks, M, true);
 }
-ChunkPlan score_lse_plan(const uc_shape& sh, const KSegs& ks, int W) {
-  return wide_path(sh, W) ? wide_plan(sh, ks, W, false) : make_plan(ks, kLseRows, kLseMaxChunks);
-}
 ChunkPlan score_col_plan(const uc_shape& sh, const KSegs& ks, int W) {
   return make_plan(ks, wide_path(sh, W) ? score_wide_chunk_rows() : 256, 1 << 30);
 }
@@ -855,9 +852,11 @@ static ChunkPlan score_mfma_plan(const KSegs& ks) {
 
 // workspace parts: pass-1 records, row normalisers (reference, 1 / sum), chunk masses (fp64),
 // and (matrix-core path) the column pass's per-group column sums (fp64);
-// every part grows monotonically with the row counts
-static void score_ws_parts(const uc_shape& sh, const KSegs& ks, int W, bool fast, size_t& part1,
-                           size_t& norm_b, size_t& mass_b, size_t& col_b) {
+// every part grows monotonically with the row counts.  fine: room for the
+// records of the binary32 path's fine cut, as far as they are few (they are
+// one per row and 256 keys at least, without bound); a call runs without them
+static void score_ws_parts(const uc_shape& sh, const KSegs& ks, int W, bool fast, bool fine,
+                           size_t& part1, size_t& norm_b, size_t& mass_b, size_t& col_b) {
   norm_b = align256((size_t)sh.B * sh.Hq * W * 2 * sizeof(float));
   col_b = 0;
   if (fast) {
@@ -874,8 +873,8 @@ static void score_ws_parts(const uc_shape& sh, const KSegs& ks, int W, bool fast
                        sizeof(double));
     return;
   }
-  part1 = std::max(generic_ws(sh, ks, kLseRows, kLseMaxChunks, W, false),
-                   wide_bytes(sh, ks, W, false));
+  part1 = generic_ws(sh, ks, kLseRows, kLseMaxChunks, W, false);
+  if (fine) part1 = std::max(part1, std::min(wide_bytes(sh, ks, W, false), kFineBytes));
   // chunks of 64 keys, or of 256 on the vector-ALU path
   mass_b = align256((size_t)sh.B * sh.Hkv * make_plan(ks, score_wide_chunk_rows(), 1 << 30).n_chunks *
                     sizeof(double));
@@ -885,10 +884,12 @@ size_t uc_score_workspace_size(const uc_shape* shape, const uc_segment* segs, in
   KSegs ks;
   if (check_segments(shape, segs, n_segs, ks) || W < 1) return 0;
   // the larger of the two paths' needs, so the size does not depend on the
-  // query dtype or the selected path
+  // query dtype or the selected path; the fine cut's records are left out
+  // where bf16 queries take the matrix-core kernels (other queries over such
+  // segments take it where those kernels' parts leave the room)
   size_t a, b, c, d, a2, b2, c2, d2;
-  score_ws_parts(*shape, ks, W, false, a, b, c, d);
-  score_ws_parts(*shape, ks, W, true, a2, b2, c2, d2);
+  score_ws_parts(*shape, ks, W, false, !score_mfma_eligible(*shape, ks, UC_BF16), a, b, c, d);
+  score_ws_parts(*shape, ks, W, true, true, a2, b2, c2, d2);
   return std::max(a + b + c + d, a2 + b2 + c2 + d2);
 }
 
@@ -906,10 +907,17 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
   if ((int64_t)shape->B * shape->Hq * W > INT32_MAX) return fail(UC_E_UNSUPPORTED, "too many query rows");
   const bool fast = score_fast(*shape, ks, q_dt);
   size_t a, b, c, d;
-  score_ws_parts(*shape, ks, W, fast, a, b, c, d);
-  const size_t need = uc_score_workspace_size(shape, segs, n_segs, W);
-  if (!ws || ws_bytes < need)
-    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  score_ws_parts(*shape, ks, W, fast, false, a, b, c, d);
+  if (!ws || ws_bytes < a + b + c + d)
+    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, a + b + c + d);
+  // the binary32 path's first pass: the fine cut where its records fit
+  bool fine = false;
+  if (!fast && wide_path(*shape, W)) {
+    size_t a2, b2, c2, d2;
+    score_ws_parts(*shape, ks, W, false, true, a2, b2, c2, d2);
+    fine = ws_bytes >= a2 + b2 + c2 + d2 && wide_bytes(*shape, ks, W, false) <= a2;
+    if (fine) a = a2;
+  }
   hipStream_t s = (hipStream_t)stream;
   float* partial = (float*)ws;
   float* norm = (float*)((char*)ws + a);
@@ -930,7 +938,7 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
     p2 = p;
   } else {
     const bool wide = wide_path(*shape, W);
-    const ChunkPlan p1 = score_lse_plan(*shape, ks, W);
+    const ChunkPlan p1 = fine ? wide_plan(*shape, ks, W, false) : make_plan(ks, kLseRows, kLseMaxChunks);
     p2 = score_col_plan(*shape, ks, W);
     e = wide ? launch_attend_wide(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s)
              : launch_attend_generic(*shape, ks, p1, q_obs, q_dt, W, sm_scale, partial, false, s);
@@ -961,10 +969,9 @@ uc_status uc_score_columns(const uc_shape* shape, const uc_segment* segs, int n_
   if (q_ld < W || q_ld > INT32_MAX) return fail(UC_E_INVALID, "q_ld=%lld < W=%d", (long long)q_ld, W);
   const bool fast = score_fast(*shape, ks, q_dt);
   size_t a, b, c, d;
-  score_ws_parts(*shape, ks, W, fast, a, b, c, d);
-  const size_t need = uc_score_workspace_size(shape, segs, n_segs, W);
-  if (!ws || ws_bytes < need)
-    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  score_ws_parts(*shape, ks, W, fast, false, a, b, c, d);
+  if (!ws || ws_bytes < a + b + c + d)
+    return fail(UC_E_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, a + b + c + d);
   float* sp[kMaxSeg] = {};
   bool any = false;
   if (scores_out)

@@ -304,6 +304,18 @@ def test_plan_workspace_after_a_path_switch(uc, M, rows):
         L.uc_plan_destroy(h)
 
 
+def test_score_workspace_is_bounded(uc):
+    """The scoring workspace holds a record per query row and 1024 keys (bf16
+    kernels) or at most 32 per row and segment (every other input) beside 8 MB
+    for a finer cut of the latter, however many query rows there are."""
+    sh, W, n = uc.uc_shape(1, 28, 4, 128), 4096, 65536
+    segs = (uc.uc_segment * 1)(_dense(uc, n))
+    rows = 28 * W
+    records = rows * (n // 1024) * 8
+    other = rows * 8 + (1024 + 4 * n // 1024) * 1024 * 8 + 4 * (n // 64) * 8  # normalisers, column sums, masses
+    assert uc.lib.uc_score_workspace_size(ctypes.byref(sh), segs, 1, W) <= records + other + 4 * 256
+
+
 def test_dynamic_budget_entry_validation(uc):
     sh = uc.uc_shape(1, 4, 2, 128)
     dense = _dense(uc, 64)

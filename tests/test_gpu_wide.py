@@ -112,3 +112,27 @@ def test_wide(case, path):
             _close(t.cpu().numpy().reshape(B, Hkv, -1), sc_ref[:, :, col:col + s.n_rows])
         col += s.n_rows
     _close(mass.cpu(), ms_ref)
+
+
+def test_scores_in_the_least_workspace():
+    """Importance scores in a workspace that holds only a coarse cut of the keys
+    (32 records per row and segment), and in the reported one."""
+    Hq, W, n, D = 2, 16, 8192 + 5, 64
+    print(f"CASE wide_least_ws n={n}", flush=True)
+    k, v, q = (rand_rows(s, *x, D, "f32") for s, x in ((1, (1, n)), (2, (1, n)), (3, (Hq, W))))
+    segs = [uc.dense_segment(dev(k, "f32").view(1, 1, n, D), dev(v, "f32").view(1, 1, n, D))]
+    shape, sm = uc.make_shape(1, Hq, 1, D), sm_scale(D)
+    want, _ = ref.score64(q.reshape(1, Hq, W, D), k[None], np.zeros(n, np.int32), 1, sm)
+    full = uc.uc_score_workspace_size(shape, segs, W)
+    parts = (Hq * W * ((n + 511) // 512) * 8, Hq * W * 8, (n + 63) // 64 * 8)  # records, normalisers, masses
+    least = sum((p + 255) // 256 * 256 for p in parts)
+    assert least < full
+    for size in (least, full):
+        out = torch.empty(1, 1, n, device="cuda")
+        uc.uc_score_importance(shape, segs, dev(q, "f32").view(1, Hq, W, D), W, sm, [out],
+                               ws=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+        _close(out.cpu(), want)
+    with pytest.raises(uc.UcError):
+        uc.uc_score_importance(shape, segs, dev(q, "f32").view(1, Hq, W, D), W, sm, [out],
+                               ws=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
