@@ -687,11 +687,11 @@ const char* uc_status_string(uc_status s);
 const char* uc_last_error(void);
 /* Name of the main kernel the calling thread's last successful launch of
  * uc_attend_mixed, uc_attend_append, uc_attend_batch or uc_score_importance
- * ran ("decode_mfma", "decode_mfma_append", "prefill_mfma", "attend_valu",
- * "decode_batch", "score_mfma", "score_valu"; "" before any).  The two
- * "_valu" names stand for the binary32 path: its matrix-core kernels under
- * UC_PATH_AUTO, the vector-ALU ones under UC_PATH_VALU.  Lets tests
- * assert the path a case reaches; static storage, never freed. */
+ * ran ("decode_mfma", "decode_mfma_append", "prefill_mfma", "attend_wide",
+ * "attend_valu", "decode_batch", "score_mfma", "score_wide", "score_valu"; ""
+ * before any; "_wide" are the binary32 matrix-core kernels, "_valu" the
+ * vector-ALU ones).  Lets tests assert the path a case reaches; static
+ * storage, never freed. */
 const char* uc_last_kernel(void);
 
 #ifdef __cplusplus

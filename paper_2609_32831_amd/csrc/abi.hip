@@ -391,7 +391,7 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs, int n_s
   }
   const ChunkPlan p = attend_plan(*shape, ks, M, ws_bytes);
   float* partial = (float*)ws;
-  g_last_kernel = "attend_valu";
+  g_last_kernel = wide_path(*shape, M) ? "attend_wide" : "attend_valu";
   hipError_t e = kernel_timer_begin(s);
   if (e == hipSuccess)
     e = wide_path(*shape, M)
@@ -928,7 +928,7 @@ uc_status uc_score_importance(const uc_shape* shape, const uc_segment* segs, int
     for (int i = 0; i < n_segs; ++i) sp[i] = scores_out[i];
   hipError_t e;
   ChunkPlan p2;
-  g_last_kernel = fast ? "score_mfma" : "score_valu";
+  g_last_kernel = fast ? "score_mfma" : wide_path(*shape, W) ? "score_wide" : "score_valu";
   if (fast) {
     const ChunkPlan p = score_mfma_plan(ks);
     e = launch_score_lse_mfma(*shape, ks, p, q_obs, W, sm_scale, partial, s);
@@ -979,7 +979,7 @@ uc_status uc_score_columns(const uc_shape* shape, const uc_segment* segs, int n_
       sp[i] = scores_out[i];
       any = any || sp[i] != nullptr;
     }
-  g_last_kernel = fast ? "score_mfma" : "score_valu";
+  g_last_kernel = fast ? "score_mfma" : wide_path(*shape, W) ? "score_wide" : "score_valu";
   if (!any && !mass_out) return ok();
   // without masses, the chunks of segments whose scores are not wanted are
   // left out of the plan (the kernels read the row counts from ks)

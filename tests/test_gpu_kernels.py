@@ -330,7 +330,7 @@ def test_score_parity_packed(case):
     sc_ref, ms_ref = ref.score64(ref.widen(q, "bf16"), K, seg_id, 2, sm_scale(D))
     shape = uc.make_shape(B, Hq, Hkv, D)
     tot = Hq // Hkv * W
-    want_kernel = "score_mfma" if G >= 32 else "score_valu"
+    want_kernel = "score_mfma" if G >= 32 else "score_wide"
     for path, kernel in ((uc.UC_PATH_AUTO, want_kernel), (uc.UC_PATH_VALU, "score_valu")):
         prev = uc.uc_set_path(path)
         try:
@@ -405,7 +405,8 @@ DCASES = [
 ]
 
 # decode cases outside the matrix-core kernel's range (groups below 32,
-# 8-bit codes): the VALU kernel serves them, and the test asserts that
+# 8-bit codes): the binary32 kernels serve them, on the matrix cores or the
+# vector ALUs by the selected path, and the test asserts that
 VCASES = [
     (1, 28, 4, 1, 16, 2, True, (300, 900, 333, 1000, 3, 8)),
     (1, 28, 4, 1, 128, 8, False, (31, 700, 129, 5000, 2, 2)),
@@ -425,7 +426,8 @@ def _decode_case(case):
 
 
 @pytest.mark.parametrize("case", VCASES, ids=[f"v{i}" for i in range(len(VCASES))])
-def test_decode_valu_parity(case):
+@pytest.mark.parametrize("kernel", ["attend_wide", "attend_valu"])
+def test_decode_valu_parity(case, kernel):
     B, Hq, Hkv, M, G, bits, per_head, sizes = case
     _print_case(test="decode_valu", B=B, Hq=Hq, Hkv=Hkv, M=M, G=G, bits=bits, sizes=sizes)
     D = 128
@@ -434,10 +436,14 @@ def test_decode_valu_parity(case):
     o = torch.empty(B, Hq, M, D, device="cuda")
     lse = torch.empty(B, Hq, M, device="cuda")
     sl = torch.empty(B, Hq, M, 4, device="cuda")
-    uc.uc_attend_mixed(shape, segs, dev(q, "bf16"), M, sm_scale(D), o, lse, sl)
-    assert uc.uc_last_kernel() == "attend_valu"
-    torch.cuda.synchronize()
-    check_attention(o.cpu().numpy(), o_ref, "valu")
+    prev = uc.uc_set_path(uc.UC_PATH_VALU if kernel == "attend_valu" else uc.UC_PATH_AUTO)
+    try:
+        uc.uc_attend_mixed(shape, segs, dev(q, "bf16"), M, sm_scale(D), o, lse, sl)
+        assert uc.uc_last_kernel() == kernel
+        torch.cuda.synchronize()
+    finally:
+        uc.uc_set_path(prev)
+    check_attention(o.cpu().numpy(), o_ref, kernel)
     assert np.allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-4)
     fin = np.isfinite(sl_ref)
     slg = sl.cpu().numpy()

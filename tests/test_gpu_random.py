@@ -52,22 +52,22 @@ def _draw(seed):
 def _expected_attend_kernel(c):
     bf = c["dt"] == "bf16" and c["D"] == 128
     if not bf:
-        return "attend_valu"
+        return "attend_wide"
     if c["G"] * c["M"] > 16:
         return "prefill_mfma"
     for s in c["segs"]:
         if s[0] == "packed":
             bits = 4 if s[4] else s[3]  # per-head widths are 2 or 4
             if s[2] < 32 or bits > 4:
-                return "attend_valu"
+                return "attend_wide"
     return "decode_mfma"
 
 
 def _expected_score_kernel(c):
     if c["dt"] != "bf16" or c["D"] != 128:
-        return "score_valu"
+        return "score_wide"
     if any(s[0] == "packed" and s[2] < 32 for s in c["segs"]):
-        return "score_valu"
+        return "score_wide"
     return "score_mfma"
 
 

@@ -90,7 +90,7 @@ def test_wide(case, path):
                 lse = torch.empty(B, Hq, M, device="cuda")
                 sl = torch.empty(B, Hq, M, n, device="cuda") if stats else None
                 uc.uc_attend_mixed(shape, segs, x, M, sm, o, lse, sl)
-                assert uc.uc_last_kernel() == "attend_valu"
+                assert uc.uc_last_kernel() == ("attend_valu" if path == "valu" else "attend_wide")
                 torch.cuda.synchronize()
                 _close(o.cpu(), o_ref)
                 assert np.allclose(lse.cpu().numpy(), lse_ref, rtol=1e-5, atol=1e-4)
@@ -102,7 +102,7 @@ def test_wide(case, path):
         scores = [torch.empty(B, Hkv, max(s.n_rows, 1), device="cuda") for s in segs]
         mass = torch.empty(B, Hkv, n, device="cuda")
         uc.uc_score_importance(shape, segs, qd, M, sm, [t if s.n_rows else None for t, s in zip(scores, segs)], mass)
-        assert uc.uc_last_kernel() == "score_valu"
+        assert uc.uc_last_kernel() == ("score_valu" if path == "valu" else "score_wide")
         torch.cuda.synchronize()
     finally:
         uc.uc_set_path(prev)
