@@ -513,15 +513,22 @@ __global__ __launch_bounds__(256, 2) void score_col_kernel(KSegs segs, ChunkPlan
   KTiles K, next;
   for (int q0 = sg * qbs * QB; q0 < q_end; q0 += QB) {
     const int nqt = min(QT, (nq - q0 + 15) / 16);
-    k_step<PACKED>(src, r0 + w0, lane, next);
+    if (!PACKED) k_step<PACKED>(src, r0 + w0, lane, next);
     __syncthreads();  // the previous block's readers are done
     stage_q(qs, qh, q0, nq, W, q_ld);
     for (int r = threadIdx.x; r < QB; r += blockDim.x)
       ls[r] = q0 + r < nq ? lh[q0 + r] : f2{INFINITY, 0.0f};  // padded rows: p = 0
     __syncthreads();
     for (int sc = r0; sc < r1; sc += SUB) {
-      K = next;
-      if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
+      if (PACKED) {
+        // decoded where they are used: holding the next step's tiles beside
+        // these spilled 36 registers (10240 keys of which 4096 in 4 bits,
+        // 28672 rows, both passes: 1693 us so, 1656 us without)
+        k_step<PACKED>(src, sc + w0, lane, K);
+      } else {
+        K = next;
+        if (sc + SUB < r1) k_step<PACKED>(src, sc + SUB + w0, lane, next);
+      }
       float cs[16];
 #pragma unroll
       for (int j = 0; j < 16; ++j) cs[j] = 0.0f;
