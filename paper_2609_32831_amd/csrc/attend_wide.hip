@@ -135,7 +135,7 @@ __device__ inline f4 tile_scores(const float (&kf)[D / 4], const float (&qf)[D /
 // in the decode kernel), then O^T += V^T P.
 template <int D, bool WANT_O>
 __device__ inline void tile_softmax(State<D>& st, const f4& s, float scale_log2, int live,
-                                    const float (&vf)[4][D / 16], int g4) {
+                                    float (&vf)[4][D / 16], int g4) {
   float p[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) p[j] = g4 + 4 * j < live ? s[j] : -INFINITY;
@@ -157,6 +157,14 @@ __device__ inline void tile_softmax(State<D>& st, const f4& s, float scale_log2,
   for (int j = 0; j < 4; ++j) p[j] = __builtin_amdgcn_exp2f(fmaf(p[j], scale_log2, -st.m));
   st.l += (p[0] + p[1]) + (p[2] + p[3]);
   if (WANT_O) {
+    if (live < ROWS) {  // rows past the end repeat the last one, with p = 0: 0 * inf must not reach the sums
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (g4 + 4 * j >= live) {
+#pragma unroll
+          for (int t = 0; t < D / 16; ++t) vf[j][t] = 0.0f;
+        }
+    }
     // the tile's product on its own, then one addition: sums of 16 rows and
     // of a few tiles round less than one running sum
     f4 pv[D / 16];
@@ -615,14 +623,17 @@ __global__ __launch_bounds__(256, 2) void score_wide_kernel(KSegs segs, ChunkPla
     const int n = min(QB, nq - q0), tiles = (n + ROWS - 1) / ROWS;
     for (int e = threadIdx.x; e < tiles * ROWS * 4; e += blockDim.x) {
       const int j = e >> 2, part = e & 3;
-      const int g = (q0 + j) / W, w = q0 + j - g * W;
+      // rows past the last repeat it: what a key gives them it gives a real row
+      // too, so that with weight 0 they add no NaN
+      const int at = q0 + min(j, n - 1);
+      const int g = at / W, w = at - g * W;
       float x[D / 4];
-      load_query<D>(q, q_dt, (int64_t)(bh * G + g) * q_ld + w, part, j < n, x);
+      load_query<D>(q, q_dt, (int64_t)(bh * G + g) * q_ld + w, part, true, x);
 #pragma unroll
       for (int i = 0; i < D / 4; i += 4)
         *reinterpret_cast<f4*>(&qs[j * QS + part * (D / 4) + i]) = f4{x[i], x[i + 1], x[i + 2], x[i + 3]};
     }
-    // rows past the window: p = exp2(-inf) = 0
+    // rows past the window: p = exp2(-inf) = 0, times 0
     if (threadIdx.x < QB)
       ls[threadIdx.x] = (int)threadIdx.x < n ? norm[(int64_t)bh * nq + q0 + threadIdx.x] : f2{INFINITY, 0.0f};
     __syncthreads();

@@ -190,8 +190,9 @@ __device__ inline void q_tile(const char* qs, int qt, int lane, u4 (&qb)[4]) {
   for (int t = 0; t < 4; ++t) qb[t] = *reinterpret_cast<const u4*>(qrow + t * 64);
 }
 
-// stage query rows [q0, q0 + QB) of the head's observation block (rows past nq
-// are zero) into LDS; row g*W + w of the block is window row w of the
+// stage query rows [q0, q0 + QB) of the head's observation block into LDS (past
+// nq the last row again: what a key gives it, infinite or not, it gives a real
+// row too, so a row of weight 0 adds no NaN that was not there); row g*W + w of the block is window row w of the
 // group's query head g, which starts ld rows after head g - 1
 __device__ inline void stage_q(char* qs, const uint16_t* qh, int q0, int nq, int W, int ld) {
   // half of a thread's chunks in flight at once: one memory latency per half,
@@ -205,7 +206,7 @@ __device__ inline void stage_q(char* qs, const uint16_t* qh, int q0, int nq, int
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int r = ((int)threadIdx.x + (e0 + j) * kThreads) / (D / 8);
-      const int at = min(q0 + r, nq - 1);  // rows past the end: a valid row, zeroed below
+      const int at = min(q0 + r, nq - 1);
       int64_t row = at;
       if (ld != W) {
         const int g = at / W;
@@ -216,7 +217,6 @@ __device__ inline void stage_q(char* qs, const uint16_t* qh, int q0, int nq, int
 #pragma unroll
     for (int j = 0; j < kBatch; ++j) {
       const int r = ((int)threadIdx.x + (e0 + j) * kThreads) / (D / 8);
-      if (q0 + r >= nq) v[j] = u4{0, 0, 0, 0};
       *reinterpret_cast<u4*>(qs + r * QROW + c * 16) = v[j];
     }
   }
@@ -326,7 +326,7 @@ __device__ inline void lse_half(const KTiles& K, const u4 (&q)[4], Pair& next, P
 // vector ALUs busy together: while the exponentials of one query tile run, the
 // logits of the next are computed, in two sets of registers taken in turn, and
 // the operands and row states of the tile after are read from LDS.  An odd last
-// tile is joined by the one after it (staged as zero rows, never read).  rm /
+// tile is joined by the one after it (staged as repeated rows, never read).  rm /
 // rl hold the wave's (m, l) per query row; the four lanes of a query column
 // agree and all store them.
 template <bool MASK>
