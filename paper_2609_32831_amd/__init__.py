@@ -154,8 +154,11 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        if torch.cuda.is_initialized():  # the current stream's handle, without a Stream object around it
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if torch.cuda.is_initialized():
+            try:  # the current stream's handle, without a Stream object around it; not a public function
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         if torch.cuda.is_available():
             return torch.cuda.current_stream().cuda_stream
         return None

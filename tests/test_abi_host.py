@@ -316,6 +316,19 @@ def test_score_workspace_is_bounded(uc):
     assert uc.lib.uc_score_workspace_size(ctypes.byref(sh), segs, 1, W) <= records + other + 4 * 256
 
 
+def test_current_stream_without_the_raw_handle(uc, monkeypatch):
+    """The current stream is found where torch lacks the (private) function that
+    gives its bare handle."""
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert uc._stream(None) == 77
+
+
 def test_dynamic_budget_entry_validation(uc):
     sh = uc.uc_shape(1, 4, 2, 128)
     dense = _dense(uc, 64)
