@@ -151,10 +151,10 @@ __global__ __launch_bounds__(256) void attend_generic_kernel(KSegs segs, ChunkPl
 // (their other fields are loaded but never used).  Per-segment log-sum-exps
 // take one more pass over m and l only.
 template <int D>
-__global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int nseg, int ps,
+__global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int nseg,
                                                             const float* __restrict__ partial,
                                                             float* o, float* lse, float* seg_lse) {
-  constexpr int PD = D / 16;  // dims per lane
+  constexpr int PD = D / 16, ps = D + 2;  // dims per lane, floats per record
   const int64_t qi = blockIdx.x;
   const int lane = threadIdx.x;
   const int C = plan.n_chunks;
@@ -174,10 +174,8 @@ __global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int 
     for (int r = 0; r < 2; ++r) {
       mc[r] = pr[r][0];
       lc[r] = pr[r][1];
-      if (o) {
 #pragma unroll
-        for (int i = 0; i < PD; ++i) oc[r][i] = pr[r][2 + d0 + i];
-      }
+      for (int i = 0; i < PD; ++i) oc[r][i] = pr[r][2 + d0 + i];
     }
     if (!two) mc[1] = -INFINITY;
 #pragma unroll
@@ -186,10 +184,8 @@ __global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int 
       const float mn = fmaxf(m, mc[r]);
       const float a = exp2f(m - mn), b = exp2f(mc[r] - mn);
       l = live ? fmaf(l, a, lc[r] * b) : l;
-      if (o) {
 #pragma unroll
-        for (int i = 0; i < PD; ++i) acc[i] = live ? fmaf(acc[i], a, oc[r][i] * b) : acc[i];
-      }
+      for (int i = 0; i < PD; ++i) acc[i] = live ? fmaf(acc[i], a, oc[r][i] * b) : acc[i];
       m = live ? mn : m;
     }
   }
@@ -200,19 +196,17 @@ __global__ __launch_bounds__(64) void attend_combine_kernel(ChunkPlan plan, int 
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
   if (lse && lane == 0) lse[qi] = (float)(((double)M + (double)log2f(l)) * kLn2d);
-  if (o) {
-    const float inv = 1.0f / l;
+  const float inv = 1.0f / l;
 #pragma unroll
-    for (int i = 0; i < PD; ++i) {
-      float v = acc[i] * sc;
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
-      acc[i] = v * inv;
-    }
-    if (rg == 0) {
+  for (int i = 0; i < PD; ++i) {
+    float v = acc[i] * sc;
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    acc[i] = v * inv;
+  }
+  if (rg == 0) {
 #pragma unroll
-      for (int i = 0; i < PD; ++i) o[qi * D + d0 + i] = acc[i];
-    }
+    for (int i = 0; i < PD; ++i) o[qi * D + d0 + i] = acc[i];
   }
   if (seg_lse) {
     for (int a = 0; a < nseg; ++a) {
@@ -462,13 +456,12 @@ hipError_t launch_attend_combine(const uc_shape& sh, const KSegs& segs, const Ch
                                  int M, const float* partial, float* o, float* lse, float* seg_lse,
                                  hipStream_t st) {
   const int64_t Q = (int64_t)sh.B * sh.Hq * M;
-  const int ps = o ? sh.D + 2 : 2;
   if (sh.D == 64)
     hipLaunchKernelGGL(attend_combine_kernel<64>, dim3((unsigned)Q), dim3(64), 0, st, plan, segs.n,
-                       ps, partial, o, lse, seg_lse);
+                       partial, o, lse, seg_lse);
   else
     hipLaunchKernelGGL(attend_combine_kernel<128>, dim3((unsigned)Q), dim3(64), 0, st, plan,
-                       segs.n, ps, partial, o, lse, seg_lse);
+                       segs.n, partial, o, lse, seg_lse);
   return hipGetLastError();
 }
 

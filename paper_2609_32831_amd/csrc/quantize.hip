@@ -10,10 +10,10 @@
 // codes and scales are reproducible bit for bit.
 //
 // Layout of the output (see unicache.h): row r of a head's codes occupies
-// D*b/8 bytes; channel c sits in byte c*b/8 at bit (c % (8/b))*b.  In the forms
-// for unaligned rows one lane owns one channel; lanes of one 32-bit word (32/b consecutive channels)
-// OR their shifted codes together with cross-lane shuffles and the first lane
-// of the word stores it, so each row's codes leave as coalesced 32-bit stores.
+// D*b/8 bytes; channel c sits in byte c*b/8 at bit (c % (8/b))*b.  A lane holds
+// 8 consecutive channels of a row (one or two 16-byte loads: rows are 16-byte
+// aligned, head dims 64 or 128, groups of at least 8) and writes their 8 codes
+// as one 16-, 32- or 64-bit store.
 #pragma clang fp contract(off)
 
 #include "uc_common.h"
@@ -27,97 +27,6 @@ __device__ inline int quant_code(float x, float mn, float s, int qmax) {
   int c = (int)rintf(t);
   return min(max(c, 0), qmax);
 }
-
-// OR-combine the shifted codes of the 32/b lanes that share a word; returns
-// the word in every lane of the group.
-__device__ inline uint32_t pack_word(int code, int c, int b) {
-  const int cpw = 32 / b;
-  uint32_t w = (uint32_t)code << ((c % cpw) * b);
-  for (int o = 1; o < cpw; o <<= 1) w |= (uint32_t)__shfl_xor((int)w, o, 64);
-  return w;
-}
-
-// Keys: block = D threads (one per channel), one block per (row group, bh).
-__global__ void quantize_k_kernel(KSeg seg, const void* __restrict__ k, int dt, int N, int D) {
-  const int g = blockIdx.x, bh = blockIdx.y, c = threadIdx.x;
-  const int G = seg.group;
-  int b;
-  int64_t off;
-  float* scale = const_cast<float*>(seg.scale_k) + ((int64_t)bh * seg.kgroups + g) * D + c;
-  float* mnp = const_cast<float*>(seg.min_k) + ((int64_t)bh * seg.kgroups + g) * D + c;
-  if (!head_codes(seg, bh, D, b, off) || (off & 15)) {
-    *scale = __builtin_nanf("");
-    return;
-  }
-  const int qmax = (1 << b) - 1;
-  const int64_t base = ((int64_t)bh * N + (int64_t)g * G) * D + c;
-  float mn = load_elem(k, dt, base), mx = mn;
-  for (int r = 1; r < G; ++r) {
-    float x = load_elem(k, dt, base + (int64_t)r * D);
-    mn = fminf(mn, x);
-    mx = fmaxf(mx, x);
-  }
-  const float s = __fdiv_rn(mx - mn, (float)qmax);
-  *scale = s;
-  *mnp = mn;
-  const int row_bytes = D * b / 8;
-  uint8_t* codes = const_cast<uint8_t*>(seg.codes_k) + off + (int64_t)g * G * row_bytes;
-  const int cpw = 32 / b;
-  for (int r = 0; r < G; ++r) {
-    int code = quant_code(load_elem(k, dt, base + (int64_t)r * D), mn, s, qmax);
-    uint32_t w = pack_word(code, c, b);
-    if (c % cpw == 0) *reinterpret_cast<uint32_t*>(codes + (int64_t)r * row_bytes + c * b / 8) = w;
-  }
-}
-
-// Values: block = 256 threads = (256 / D) rows x D channels; group min/max
-// through LDS.
-__global__ void quantize_v_kernel(KSeg seg, const void* __restrict__ v, int dt, int N, int D) {
-  __shared__ float xs[256];
-  __shared__ float ss[256], ms[256];
-  const int rows_per_block = 256 / D;
-  const int lr = threadIdx.x / D, c = threadIdx.x % D;
-  const int r = blockIdx.x * rows_per_block + lr, bh = blockIdx.y;
-  const int G = seg.group, ngv = D / G;
-  int b;
-  int64_t off;
-  const bool ok = head_codes(seg, bh, D, b, off) && !(off & 15);
-  const bool live = r < seg.n_full;
-  float x = live ? load_elem(v, dt, ((int64_t)bh * N + r) * D + c) : 0.0f;
-  xs[threadIdx.x] = x;
-  __syncthreads();
-  if (live && c % G == 0) {
-    float mn = xs[threadIdx.x], mx = mn;
-    for (int i = 1; i < G; ++i) {
-      float y = xs[threadIdx.x + i];
-      mn = fminf(mn, y);
-      mx = fmaxf(mx, y);
-    }
-    const float s = ok ? __fdiv_rn(mx - mn, (float)((1 << b) - 1)) : __builtin_nanf("");
-    ss[threadIdx.x] = s;
-    ms[threadIdx.x] = mn;
-    const int64_t mi = ((int64_t)bh * seg.cap_full + r) * ngv + c / G;
-    const_cast<float*>(seg.scale_v)[mi] = s;
-    const_cast<float*>(seg.min_v)[mi] = mn;
-  }
-  __syncthreads();
-  if (!ok) return;  // uniform over the block: bh is per block
-  const int gl = threadIdx.x - (c % G);
-  const int code = live ? quant_code(x, ms[gl], ss[gl], (1 << b) - 1) : 0;
-  const uint32_t w = pack_word(code, c, b);
-  const int cpw = 32 / b;
-  if (live && c % cpw == 0) {
-    const int row_bytes = D * b / 8;
-    uint8_t* codes = const_cast<uint8_t*>(seg.codes_v) + off + (int64_t)r * row_bytes;
-    *reinterpret_cast<uint32_t*>(codes + c * b / 8) = w;
-  }
-}
-
-// ---- vectorised forms for head dims 64 / 128: a lane holds 8 consecutive
-// channels of a row (one or two 16-byte loads) and writes their 8 codes as one
-// 16-, 32- or 64-bit store.  Min and max are exact and the scale and the codes
-// are those of quant_code, so the results are the same bits as the per-element
-// forms above.
 
 // Eight elements of a row as loaded (16-byte aligned).
 template <int DT>
@@ -567,25 +476,15 @@ hipError_t launch_quantize(const uc_shape& sh, const void* k, const void* v, int
                            const KSeg& out, hipStream_t st) {
   const int BH = sh.B * sh.Hkv, D = sh.D;
   if (out.n_full > 0) {
-    // the vectorised kernel: head dim 64 or 128, 16-byte aligned rows, groups
-    // of at least the 8 channels a lane holds; the others an element per lane
-    const bool vec = (D == 64 || D == 128) && out.group >= 8 && !((uintptr_t)k & 15) && !((uintptr_t)v & 15);
     const int groups = out.n_full / out.group;
-    if (vec) {
-      const int rows = kVRows * 256 / (D / 8);
-      auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(groups + (out.n_full + rows - 1) / rows, BH), dim3(256), 0,
-                           st, out, k, v, N, groups);
-      };
-      if (dt == UC_F32) D == 64 ? go(quantize_vec_kernel<UC_F32, 64>) : go(quantize_vec_kernel<UC_F32, 128>);
-      else if (dt == UC_F16) D == 64 ? go(quantize_vec_kernel<UC_F16, 64>) : go(quantize_vec_kernel<UC_F16, 128>);
-      else D == 64 ? go(quantize_vec_kernel<UC_BF16, 64>) : go(quantize_vec_kernel<UC_BF16, 128>);
-    } else {
-      hipLaunchKernelGGL(quantize_k_kernel, dim3(groups, BH), dim3(D), 0, st, out, k, dt, N, D);
-      const int rpb = 256 / D;
-      hipLaunchKernelGGL(quantize_v_kernel, dim3((out.n_full + rpb - 1) / rpb, BH), dim3(256), 0,
-                         st, out, v, dt, N, D);
-    }
+    const int rows = kVRows * 256 / (D / 8);
+    auto go = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(groups + (out.n_full + rows - 1) / rows, BH), dim3(256), 0,
+                         st, out, k, v, N, groups);
+    };
+    if (dt == UC_F32) D == 64 ? go(quantize_vec_kernel<UC_F32, 64>) : go(quantize_vec_kernel<UC_F32, 128>);
+    else if (dt == UC_F16) D == 64 ? go(quantize_vec_kernel<UC_F16, 64>) : go(quantize_vec_kernel<UC_F16, 128>);
+    else D == 64 ? go(quantize_vec_kernel<UC_BF16, 64>) : go(quantize_vec_kernel<UC_BF16, 128>);
   }
   if (out.tail_len > 0) {
     const int row_bytes = D * dtype_bytes(dt);
