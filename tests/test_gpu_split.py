@@ -1,9 +1,11 @@
 """Multi-query attention with the keys split among workgroups (calls whose
-query blocks leave CUs idle): one tile short of and past the number of tiles
-that gives two splits, splits that end inside a segment, a packed segment's
-residual tail and partial tiles at a split's end, and per-segment statistics
-of segments that only some splits see.  The allocation-free call gives the
-workspace call's bits.
+query blocks leave CUs idle): one key tile short of the number from which
+calls are split and exactly that many, splits that end inside a segment, a
+packed segment's residual tail and partial tiles at a split's end, and
+per-segment statistics of segments that only some splits see.  The
+allocation-free call gives the workspace call's bits.  Whether a call was split
+shows in its workspace: the splits' records lie behind what a plan, which
+never splits, needs.
 
 Tolerance: the attention bar; lse as in the other prefill tests."""
 import numpy as np
@@ -19,19 +21,22 @@ import oracle as ref  # noqa: E402
 import paper_2609_32831_amd as uc  # noqa: E402
 from gpu_util import check_attention, dev, mixed_case, rand_rows, sm_scale  # noqa: E402
 
-# B, Hq, Hkv, M, sizes (text, vit_full, vit_keep, pack, tail, cap)
+# B, Hq, Hkv, M, sizes (text, vit_full, vit_keep, pack, tail, cap), whether the keys are split
 CASES = [
-    (1, 7, 1, 3, (480, 10, 0, 0, 0, 1)),            # 15 tiles: unsplit
-    (1, 7, 1, 3, (481, 10, 0, 0, 0, 1)),            # 16 tiles: two splits, the last tile partial
-    (1, 7, 1, 37, (33, 400, 300, 640 + 17, 5, 8)),  # views that end inside a split
-    (2, 8, 2, 40, (1000, 2000, 1777, 2048 + 63, 100, 128)),
-    (1, 28, 4, 203, (100, 900, 1024, 4096, 3, 8)),  # the records exceed the static array
+    (1, 7, 1, 3, (992, 10, 0, 0, 0, 1), False),            # 31 tiles
+    (1, 7, 1, 3, (961, 10, 0, 0, 0, 1), False),            # 31 tiles, the last of one row
+    (1, 7, 1, 3, (993, 10, 0, 0, 0, 1), True),             # 32 tiles, the last of one row
+    (1, 7, 1, 3, (1024, 10, 0, 0, 0, 1), True),            # 32 whole tiles
+    (1, 7, 1, 37, (33, 400, 300, 640 + 17, 5, 8), True),   # views that end inside a split
+    (2, 8, 2, 40, (1000, 2000, 1777, 2048 + 63, 100, 128), True),
+    (1, 28, 4, 203, (100, 900, 1024, 4096, 3, 8), True),   # records of 30 MB
+    (1, 28, 4, 1180, (600, 500, 400, 0, 3, 8), False),     # 260 query blocks: the chip is full
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[f"s{i}" for i in range(len(CASES))])
 def test_split(case):
-    B, Hq, Hkv, M, sizes = case
+    B, Hq, Hkv, M, sizes, split = case
     print(f"CASE split {case}", flush=True)
     D = 128
     segs, K, V, ids = mixed_case(B, Hq, Hkv, D, "bf16", sizes[:1] + (max(sizes[1], sizes[2]),) + sizes[2:], seed=M)
@@ -39,6 +44,13 @@ def test_split(case):
     sm, shape, qd = sm_scale(D), uc.make_shape(B, Hq, Hkv, D), dev(q, "bf16")
     o_ref, lse_ref, sl_ref, _ = ref.attend(ref.widen(q, "bf16"), K, V, None, ids, 4, sm)
     fin = np.isfinite(sl_ref)
+    plan = uc.AttendPlan(shape, segs, None, torch.bfloat16, M, sm)
+    unsplit = int(uc.lib.uc_plan_workspace_size(plan._h))
+    plan.close()
+    ws = torch.full((uc.uc_attend_workspace_size(shape, segs, uc.UC_BF16, M),), 171, dtype=torch.uint8, device="cuda")
+    uc.uc_attend_mixed(shape, segs, qd, M, sm, torch.empty(B, Hq, M, D, device="cuda"), ws=ws)
+    torch.cuda.synchronize()
+    assert bool((ws[unsplit:] != 171).any()) == split
     seen = {}
     for call in (uc.uc_attend_mixed, uc.uc_attend_mixed_noalloc):
         for stats in (True, False):
