@@ -312,7 +312,7 @@ uc_status uc_attend_mixed(const uc_shape* shape, const uc_segment* segs,
  * HIP graph capture, tight serving loops, harnesses that forbid allocation):
  * the same computation, kernels and results, with the workspace taken from
  * a static device array that the library holds on every GPU it runs on until
- * the process ends (UC_SCRATCH_BYTES, and 35 MB for the partial results of
+ * the process ends (UC_SCRATCH_BYTES, and 35 MiB for the partial results of
  * calls that split their keys).  The call allocates nothing
  * (no hipMalloc, no allocating library routine); the caller still passes q,
  * o and the optional lse / seg_lse.  A call that needs more than

@@ -25,11 +25,12 @@
 // none of which depends on another, so one wave keeps the matrix cores and
 // the vector ALUs busy at once; the probability operands of consecutive
 // tiles alternate between two register sets.  The rare raise of the reference
-// maximum runs
-// after the matrix instructions (it rescales the accumulators they update).
+// maximum, and the mask of a tile that a segment's end leaves partial, run
+// after the matrix instructions (a raise rescales the accumulators they update).
 // Outputs (normalised O, lse, per-segment lse) are written directly; only a
-// call with too few query blocks for the chip splits the keys (Split).  Workgroups are mapped so that those of one (b, h_kv) run
-// on the same XCD and share its L2 copy of the head's rows.
+// call with too few query blocks for the chip splits the keys (Split).
+// Workgroups are mapped so that those of one (b, h_kv) run on the same XCD and
+// share its L2 copy of the head's rows.
 //
 // Packed segments first go through prepare_kernel: codes -> round_to_bf16(
 // fmaf(code, scale, min)) into a [B, Hkv, n_full, D] bf16 workspace (once per
@@ -89,7 +90,9 @@ struct Views {
 // its first tile, so a probability is rounded to the same 16 bits however the
 // keys are split (references of the splits' own moved the results of 203 query
 // rows over 6144 by 2.7e-4, as much as that rounding itself); what is left is
-// the order of the sums, and rows whose reference is raised later on.
+// the order of the sums, and rows whose reference is raised later on (3e-5 to
+// 8e-5 over calls of 3 to 1000 query rows with outlier keys).  It costs a call
+// of 203 rows 0.6 us of 48.
 struct Split {
   int n, per;
   float* ml;

@@ -20,10 +20,11 @@
 // in flight while it computes the current one.
 //
 // Bound: these calls are short, and a wave-per-row kernel on the vector ALUs
-// spent six dependent cross-lane sums on every row.  Measured on one MI355X
-// (4 requests, 28 query heads on 4 KV heads, head dim 128, fp16, 512 dense
-// rows and 4096 8-bit rows, one decode step): 171 us before, MEASURED_WIDE_A
-// now; fp32, head dim 64, 371 rows, one KV head: MEASURED_WIDE_B.
+// spent six dependent cross-lane sums on every row.  Measured on one MI355X, one
+// decode step, kernel times: 4 requests, 28 query heads on 4 KV heads, head dim
+// 128, fp16, 577 dense rows and 4096 8-bit rows 165.8 us before, 22.6 now (and
+// the merge of their records 4.7 and 4.6); fp32, head dim 64, 4 query heads on
+// one KV head, 371 rows 31.6 us before, 5.2 now (merge 4.6 and 1.8).
 #include "uc_common.h"
 
 namespace uc {

@@ -20,7 +20,8 @@
 // A-operand layout; packed rows decoded in registers to their stored bf16
 // values) and runs each pair against every 16-row query tile of the block,
 // whose B operands it reads from the block staged in LDS.  The next pair is
-// loaded while the current one is computed.  Logits are in base 2 (q.k times
+// loaded while the current one is computed (but for packed rows in pass 2,
+// whose registers would spill).  Logits are in base 2 (q.k times
 // scale*log2(e)).
 // Row normalisers: a record is (m, l), l the sum of exp2(s - m), with m a
 // reference that is at most kLazy below the row's maximum; the records of a
