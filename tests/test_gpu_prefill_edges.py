@@ -21,7 +21,7 @@ import workloads as gen  # noqa: E402
 from gpu_util import check_attention, dev, rand_rows, sm_scale  # noqa: E402
 
 
-@pytest.mark.parametrize("rows", [(33,), (5, 64), (100, 70, 32), (40, 1100, 7)], ids=str)
+@pytest.mark.parametrize("rows", [(33,), (5, 64), (100, 70, 32), (40, 1100, 7), (5, 1100)], ids=str)
 def test_logits_far_below_zero(rows):
     print(f"CASE low_logits {rows}", flush=True)
     B, Hq, Hkv, M, D = 1, 4, 1, 20, 128
